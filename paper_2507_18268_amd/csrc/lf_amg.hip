@@ -242,7 +242,7 @@ k_amg_sweep_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__re
     if (st->done) return;
     typedef Lanes<double, 2> R;
     double acc[1] = {0.0};
-    box_walk_xs<double, 2, false, false>(L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &xc, const R &dg) {
+    box_walk_xs<double, 2, false, false>(static_cast<int32_t>(blockIdx.x), L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &xc, const R &dg) {
         const R bc = lanes_load<double, 2>(b, c);
         R v;
 #pragma unroll
@@ -275,7 +275,7 @@ k_amg_restrict_box(BandLayout<3> L, BoxWalk bw, const double *__restrict__ diag,
     R res[2][2];
     // the walk visits a tile's rows line by line, within a line plane by plane
     int call = 0;
-    box_walk<double, 2, false, false>(L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &, const R &) {
+    box_walk<double, 2, false, false>(static_cast<int32_t>(blockIdx.x), L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &, const R &) {
         const R bb = lanes_load<double, 2>(b, c);
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)

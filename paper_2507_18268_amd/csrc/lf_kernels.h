@@ -54,6 +54,19 @@ __device__ __forceinline__ int32_t cell_row(int j) {
     return cell_row_at<R>(static_cast<int32_t>(blockIdx.x), j);
 }
 
+// Order in which a launch walks its workgroups' shares.  A vector of a large
+// mesh (134 MB at 256^3) passes through a 256 MB last-level cache: what a
+// kernel touched last is still there when the next one starts, what it touched
+// first is not.  Consecutive kernels of a solve therefore walk the mesh in
+// opposite directions: workgroup b takes the share of its mirror image, in
+// groups of eight so that a share stays on its die (workgroups go round the
+// eight dies).  Shares keep their own partial slot, so every sum is the one of
+// the forward walk.
+__device__ __forceinline__ int32_t walk_share(bool backward) {
+    const int32_t b = static_cast<int32_t>(blockIdx.x), g8 = static_cast<int32_t>(gridDim.x) & ~7;
+    return backward && b < g8 ? (g8 - 8 - (b & ~7)) | (b & 7) : b;
+}
+
 // first stage: the workgroup's partial sums go to part[slot * G + blockIdx.x]
 // (BS: threads of the workgroup; _at: the workgroup's index blk within its
 // problem's launch, for launches that serve several problems)
@@ -612,10 +625,10 @@ struct Rb2Lane {
     bool tv, below_ok, above_ok, zlo, zhi, ylo, yhi;
 };
 
-__device__ __forceinline__ Rb2Lane rb2_lane(const RBForm &f) {
+__device__ __forceinline__ Rb2Lane rb2_lane(int32_t blk, const RBForm &f) {
     Rb2Lane l;
     const int64_t nr = f.nr, h = f.h, H = f.H;
-    l.u = 2 * (static_cast<int64_t>(blockIdx.x) * kCellBlock + threadIdx.x);
+    l.u = 2 * (static_cast<int64_t>(blk) * kCellBlock + threadIdx.x);
     l.tv = l.u < nr;
     const int key = l.tv ? static_cast<int>(l.u) : -8;
     l.below_ok = lane_from_below(key, -1000) == key - 2;
@@ -630,12 +643,12 @@ __device__ __forceinline__ Rb2Lane rb2_lane(const RBForm &f) {
 }
 
 template <class Fn>
-__device__ __forceinline__ void rb2_product(const RBForm &f, const double *__restrict__ diagB,
+__device__ __forceinline__ void rb2_product(int32_t blk, const RBForm &f, const double *__restrict__ diagB,
                                             const double *__restrict__ coef, const double *__restrict__ p,
                                             Fn &&fn) {
     typedef Lanes<double, 2> R;
     const int64_t nr = f.nr, h = f.h, H = f.H;
-    const Rb2Lane l = rb2_lane(f);
+    const Rb2Lane l = rb2_lane(blk, f);
     const int64_t u = l.u, pos = l.pos;
     const bool tv = l.tv, below_ok = l.below_ok, above_ok = l.above_ok;
     const int32_t par = l.par;
@@ -747,12 +760,13 @@ struct MemX {
 // All lanes of a wave run the lane exchanges, so the caller must not branch
 // around the call.
 template <class T, int W, bool kStream, bool kUnitDiag, class XS, class Fn>
-__device__ __forceinline__ void box_walk_xs(const BandLayout<3> &L, const BoxWalk &bw, const T *__restrict__ diag,
-                                            const T *__restrict__ coef, const XS &x, Fn &&fn) {
+__device__ __forceinline__ void box_walk_xs(int32_t blk, const BandLayout<3> &L, const BoxWalk &bw,
+                                            const T *__restrict__ diag, const T *__restrict__ coef, const XS &x,
+                                            Fn &&fn) {
     typedef Lanes<T, W> R;
     constexpr int kBwY = bw_lines(W), kBwZ = bw_planes(W);
     const int64_t n = L.n, d1 = L.d[1], d2 = L.d[2];
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBwBlock + threadIdx.x;
+    const int64_t i = static_cast<int64_t>(blk) * kBwBlock + threadIdx.x;
     const int64_t g = i / bw.hx, t = i - g * bw.hx;
     const bool tv = g < bw.ntiles;
     const int64_t yb = g % bw.nyb, zb = g / bw.nyb;
@@ -855,9 +869,10 @@ __device__ __forceinline__ void box_walk_xs(const BandLayout<3> &L, const BoxWal
 }
 
 template <class T, int W, bool kStream, bool kUnitDiag, class Fn>
-__device__ __forceinline__ void box_walk(const BandLayout<3> &L, const BoxWalk &bw, const T *__restrict__ diag,
-                                         const T *__restrict__ coef, const T *__restrict__ x, Fn &&fn) {
-    box_walk_xs<T, W, kStream, kUnitDiag>(L, bw, diag, coef, MemX<T, W>{x}, fn);
+__device__ __forceinline__ void box_walk(int32_t blk, const BandLayout<3> &L, const BoxWalk &bw,
+                                         const T *__restrict__ diag, const T *__restrict__ coef,
+                                         const T *__restrict__ x, Fn &&fn) {
+    box_walk_xs<T, W, kStream, kUnitDiag>(blk, L, bw, diag, coef, MemX<T, W>{x}, fn);
 }
 
 // ---------------------------------------------------------------------------

@@ -152,7 +152,7 @@ __device__ __forceinline__ void mx_direction(int32_t blk, const SolverParams &sp
 __global__ void __launch_bounds__(kCellBlock)
 k_mx_direction(SolverParams sp, const float *__restrict__ r32, float *__restrict__ p32, float *__restrict__ d32,
                const PcgState *__restrict__ st) {
-    mx_direction(static_cast<int32_t>(blockIdx.x), sp, r32, p32, d32, st);
+    mx_direction(walk_share((st->inner_iter & 1) != 0), sp, r32, p32, d32, st);
 }
 
 // q = As p in FP32 (unit diagonal: p_c first, then the row's entries in
@@ -206,14 +206,15 @@ k_mx_amul_dot_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const float *__r
                   const PcgState *__restrict__ st) {
     if (inner_off(st)) return;
     typedef Lanes<float, 4> R;
+    const int32_t blk = walk_share((st->inner_iter & 1) == 0);
     double acc[1] = {0.0};
-    box_walk<float, 4, false, true>(L, bw, nullptr, coef32, p32, [&](int64_t c, const R &qc, const R &pc, const R &) {
+    box_walk<float, 4, false, true>(blk, L, bw, nullptr, coef32, p32, [&](int64_t c, const R &qc, const R &pc, const R &) {
         lanes_store_stream(q32, c, qc);
 #pragma unroll
         for (int w = 0; w < 4; ++w) acc[0] += static_cast<double>(qc.v[w]) * static_cast<double>(pc.v[w]);
     });
     const int slots[1] = {kPartPq};
-    write_partials<1, kBwBlock>(part, sp.grid_mx, slots, acc);
+    write_partials_at<1, kBwBlock>(part, sp.grid_mx, blk, slots, acc);
 }
 
 // rs -= alpha q (FP32); FP64 partials of the L1 norm s|rs| and of rs.rs
@@ -239,7 +240,7 @@ __device__ __forceinline__ void mx_update(int32_t blk, const SolverParams &sp, c
 __global__ void __launch_bounds__(kCellBlock)
 k_mx_update(SolverParams sp, const float *__restrict__ q32, const float *__restrict__ sig32,
             float *__restrict__ r32, double *__restrict__ part, const PcgState *__restrict__ st) {
-    mx_update(static_cast<int32_t>(blockIdx.x), sp, q32, sig32, r32, part, st);
+    mx_update(walk_share((st->inner_iter & 1) != 0), sp, q32, sig32, r32, part, st);
 }
 
 // T += d = (y + alpha p) / s in FP64, alpha p being the last inner update
@@ -336,10 +337,11 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
                   double *__restrict__ part, const PcgState *__restrict__ st) {
     if (st->done) return;
     const bool keep = st->inner_iter > 0;
+    const int32_t blk = walk_share(true);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     typedef Lanes<double, 2> R;
     typedef float F2 __attribute__((ext_vector_type(2)));
-    box_walk<double, 2, true, false>(L, bw, diagB, coef, T, [&](int64_t c, const R &ax, const R &, const R &db) {
+    box_walk<double, 2, true, false>(blk, L, bw, diagB, coef, T, [&](int64_t c, const R &ax, const R &, const R &db) {
         // the two rows as pass_end_row takes them, with 16- and 8-byte accesses
         const R b = lanes_load<double, 2>(srcB, c);
         const F2 pp = keep ? *reinterpret_cast<const F2 *>(p32 + c) : F2{0.0f, 0.0f};
@@ -359,7 +361,7 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
         *reinterpret_cast<F2 *>(d32 + c) = F2{0.0f, 0.0f};
     });
     const int slots[4] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32};
-    write_partials<4, kBwBlock>(part, sp.grid, slots, acc);
+    write_partials_at<4, kBwBlock>(part, sp.grid, blk, slots, acc);
 }
 
 // one-workgroup decisions of the refinement
@@ -679,7 +681,7 @@ __global__ void __launch_bounds__(kBwBlock)
 k_mx_amul_box_hook(BandLayout<3> L, BoxWalk bw, const float *__restrict__ coef32, const float *__restrict__ x,
                    float *__restrict__ y) {
     typedef Lanes<float, 4> R;
-    box_walk<float, 4, false, true>(L, bw, nullptr, coef32, x, [&](int64_t c, const R &yc, const R &, const R &) {
+    box_walk<float, 4, false, true>(static_cast<int32_t>(blockIdx.x), L, bw, nullptr, coef32, x, [&](int64_t c, const R &yc, const R &, const R &) {
 #pragma unroll
         for (int w = 0; w < 4; ++w) y[c + w] = yc.v[w];
     });
@@ -720,7 +722,7 @@ k_mx_scale2(BandLayout<K> L, const float *__restrict__ sig32, const double *__re
     typedef float F2 __attribute__((ext_vector_type(2)));
     typedef double D2 __attribute__((ext_vector_type(2)));
     const int64_t n = L.n;
-    const int64_t c = 2 * (static_cast<int64_t>(blockIdx.x) * kCellBlock + threadIdx.x);
+    const int64_t c = 2 * (static_cast<int64_t>(walk_share(true)) * kCellBlock + threadIdx.x);
     if (c >= n) return;
     const F2 sv = *reinterpret_cast<const F2 *>(sig32 + c);
     const double sc[2] = {static_cast<double>(sv.x), static_cast<double>(sv.y)};

@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(kBwBlock)
 k_amul_box(BandLayout<3> L, BoxWalk bw, const double *__restrict__ diagB, const double *__restrict__ coef,
            const double *__restrict__ x, double *__restrict__ y) {
     typedef Lanes<double, 2> R;
-    box_walk<double, 2, false, false>(L, bw, diagB, coef, x, [&](int64_t c, const R &yc, const R &, const R &) {
+    box_walk<double, 2, false, false>(static_cast<int32_t>(blockIdx.x), L, bw, diagB, coef, x, [&](int64_t c, const R &yc, const R &, const R &) {
         y[c] = yc.v[0];
         y[c + 1] = yc.v[1];
     });
@@ -269,7 +269,7 @@ k_direction(SolverParams sp, const double *__restrict__ rD, const double *__rest
     if (st->done) return;
     const bool first = st->n_iter == 0;
     const double beta = st->beta, alpha = st->alpha;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
+    const int32_t c = walk_share(!kDiag) * kCellBlock + static_cast<int32_t>(threadIdx.x);
     if (c < sp.n) {
         const double wc = kDiag ? __builtin_nontemporal_load(&rD[c]) * r[c] : w[c];
         if (first) {
@@ -325,9 +325,10 @@ k_amul_dot_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__res
                const double *__restrict__ coef, const double *__restrict__ p, double *__restrict__ q,
                double *__restrict__ part, const PcgState *__restrict__ st) {
     if (st->done) return;
+    const int32_t blk = static_cast<int32_t>(blockIdx.x);
     double acc[1] = {0.0};
     typedef Lanes<double, 2> R;
-    box_walk<double, 2, true, false>(L, bw, diagB, coef, p, [&](int64_t c, const R &qc, const R &pc, const R &) {
+    box_walk<double, 2, true, false>(blk, L, bw, diagB, coef, p, [&](int64_t c, const R &qc, const R &pc, const R &) {
         lanes_store_stream(q, c, qc);
         acc[0] += qc.v[0] * pc.v[0];
         acc[0] += qc.v[1] * pc.v[1];
@@ -514,7 +515,7 @@ k_scale_coef(BandLayout<3> L, const double *__restrict__ sd, const double *__res
              double *__restrict__ coefS) {
     typedef Lanes<double, 2> R;
     const int64_t n = L.n;
-    const int64_t c = 2 * (static_cast<int64_t>(blockIdx.x) * kCellBlock + threadIdx.x);
+    const int64_t c = 2 * (static_cast<int64_t>(walk_share(true)) * kCellBlock + threadIdx.x);
     if (c >= n) return;
     const R s = lanes_load<double, 2>(sd, c);
     R sn[3];
@@ -539,15 +540,18 @@ k_amul_dot_box_scaled(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double
                       const double *__restrict__ p, double *__restrict__ q, double *__restrict__ part,
                       const PcgState *__restrict__ st) {
     if (st->done) return;
+    const int32_t blk = walk_share((st->n_iter & 1) != 0);
     double acc[1] = {0.0};
     typedef Lanes<double, 2> R;
-    box_walk<double, 2, false, true>(L, bw, nullptr, coefS, p, [&](int64_t c, const R &qc, const R &pc, const R &) {
-        lanes_store_stream(q, c, qc);
+    box_walk<double, 2, false, true>(blk, L, bw, nullptr, coefS, p, [&](int64_t c, const R &qc, const R &pc, const R &) {
+        // q~ stays cached: the update starts where this walk ends (update 85 ->
+        // 82 us at 256^3 against a streamed store)
+        *reinterpret_cast<Lanes<double, 2>::vec *>(q + c) = Lanes<double, 2>::vec{qc.v[0], qc.v[1]};
         acc[0] += qc.v[0] * pc.v[0];
         acc[0] += qc.v[1] * pc.v[1];
     });
     const int slots[1] = {kPartPq};
-    write_partials<1, kBwBlock>(part, sp.grid, slots, acc);
+    write_partials_at<1, kBwBlock>(part, sp.grid, blk, slots, acc);
 }
 
 // r~ -= alpha q~; partial sums of |sd r~| (the residual of A) and of r~.r~
@@ -559,11 +563,12 @@ k_update_scaled(SolverParams sp, const double *__restrict__ q, double *__restric
     if (st->done) return;
     typedef Lanes<double, 2> R;
     typedef Lanes<double, 2>::vec V;
+    const int32_t blk = walk_share((st->n_iter & 1) == 0);
     const double alpha = st->alpha;
     double acc[2] = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < kUpdRows / 2; ++j) {
-        const int64_t c = 2 * static_cast<int64_t>(cell_row<kUpdRows / 2>(j));
+        const int64_t c = 2 * static_cast<int64_t>(cell_row_at<kUpdRows / 2>(blk, j));
         if (c >= sp.n) continue;
         const R qc = lanes_load<double, 2, true>(q, c);
         const R sc = lanes_load<double, 2, true>(sd, c);
@@ -579,7 +584,7 @@ k_update_scaled(SolverParams sp, const double *__restrict__ q, double *__restric
         *reinterpret_cast<V *>(r + c) = y;
     }
     const int slots[2] = {kPartSumR, kPartWr};
-    write_partials<2>(part, sp.grid, slots, acc);
+    write_partials_at<2>(part, sp.grid, blk, slots, acc);
 }
 
 // p~ = r~ + beta p~ with the deferred x~ += alpha p~ of the iteration before,
@@ -592,10 +597,11 @@ k_direction_scaled(SolverParams sp, const double *__restrict__ r, double *__rest
     typedef Lanes<double, 2> R;
     typedef Lanes<double, 2>::vec V;
     const bool first = st->n_iter == 0;
+    const int32_t blk = walk_share((st->n_iter & 1) == 0);
     const double beta = st->beta, alpha = st->alpha;
 #pragma unroll
     for (int j = 0; j < kUpdRows / 2; ++j) {
-        const int64_t c = 2 * static_cast<int64_t>(cell_row<kUpdRows / 2>(j));
+        const int64_t c = 2 * static_cast<int64_t>(cell_row_at<kUpdRows / 2>(blk, j));
         if (c >= sp.n) continue;
         const R rc = lanes_load<double, 2>(r, c);
         V pn;
@@ -627,7 +633,8 @@ k_commit_scaled(SolverParams sp, double *__restrict__ T, const double *__restric
     const bool moved = st->n_iter >= 1;
     const bool apply = !(st->n_iter < 1 || st->singular || st->nonfinite);
     const double alpha = st->alpha;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
+    const int32_t blk = walk_share((st->n_iter & 1) == 0);
+    const int32_t c = blk * kCellBlock + static_cast<int32_t>(threadIdx.x);
     double acc[1] = {0.0};
     if (c < sp.n) {
         double tc;
@@ -643,7 +650,7 @@ k_commit_scaled(SolverParams sp, double *__restrict__ T, const double *__restric
         acc[0] = tc;
     }
     const int slots[1] = {kPartSumX};
-    write_partials<1>(part, sp.grid, slots, acc);
+    write_partials_at<1>(part, sp.grid, blk, slots, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1013,7 +1020,7 @@ k_amul_dot_rb2(SolverParams sp, RBLayout L, const double *__restrict__ diagB, co
     typedef Lanes<double, 2> R;
     const int64_t nr = L.f.nr;
     double acc[1] = {0.0};
-    rb2_product(L.f, diagB, coef, p, [&](int64_t u, const R &qr, const R &qb, const R &pr, const R &pb) {
+    rb2_product(static_cast<int32_t>(blockIdx.x), L.f, diagB, coef, p, [&](int64_t u, const R &qr, const R &qb, const R &pr, const R &pb) {
         lanes_store_stream(q, u, qr);
         lanes_store_stream(q, nr + u, qb);
         acc[0] += qr.v[0] * pr.v[0] + qb.v[0] * pb.v[0];
@@ -1029,7 +1036,7 @@ k_amul_rb2(RBLayout L, const double *__restrict__ diagB, const double *__restric
            const double *__restrict__ x, double *__restrict__ y) {
     typedef Lanes<double, 2> R;
     const int64_t nr = L.f.nr;
-    rb2_product(L.f, diagB, coef, x, [&](int64_t u, const R &qr, const R &qb, const R &, const R &) {
+    rb2_product(static_cast<int32_t>(blockIdx.x), L.f, diagB, coef, x, [&](int64_t u, const R &qr, const R &qb, const R &, const R &) {
         y[u] = qr.v[0];
         y[u + 1] = qr.v[1];
         y[nr + u] = qb.v[0];
@@ -1061,7 +1068,7 @@ k_assemble_rb2(SolverParams sp, double rdt, double DT, RBLayout L, const int32_t
     typedef typename R::vec RV;
     const RBForm &f = L.f;
     const int64_t nr = f.nr, h = f.h, H = f.H;
-    const Rb2Lane l = rb2_lane(f);
+    const Rb2Lane l = rb2_lane(static_cast<int32_t>(blockIdx.x), f);
     const int64_t u = l.u, pos = l.pos;
     const int32_t par = l.par;
     const R z = lanes_zero<double, 2>();
@@ -1248,7 +1255,7 @@ k_dic_rd_rb2(RBLayout L, const double *__restrict__ diagB, const double *__restr
     typedef Lanes<double, 2> R;
     const RBForm &f = L.f;
     const int64_t nr = f.nr, h = f.h, H = f.H;
-    const Rb2Lane l = rb2_lane(f);
+    const Rb2Lane l = rb2_lane(walk_share(true), f);
     const int64_t u = l.u, pos = l.pos;
     const int32_t par = l.par;
     const R z = lanes_zero<double, 2>();
@@ -1321,7 +1328,8 @@ k_dic_forward_rb2(SolverParams sp, RBLayout L, const double *__restrict__ coef, 
     const RBForm &f = L.f;
     const int64_t nr = f.nr, h = f.h, H = f.H;
     const double alpha = kUpdate ? st->alpha : 0.0;
-    const Rb2Lane l = rb2_lane(f);
+    const int32_t blk = walk_share(kUpdate);
+    const Rb2Lane l = rb2_lane(blk, f);
     const int64_t u = l.u, pos = l.pos;
     const int32_t par = l.par;
     const R z = lanes_zero<double, 2>();
@@ -1402,7 +1410,7 @@ k_dic_forward_rb2(SolverParams sp, RBLayout L, const double *__restrict__ coef, 
     }
     if (kUpdate) {
         const int slots[1] = {kPartSumR};
-        write_partials<1>(part, sp.grid, slots, acc);
+        write_partials_at<1>(part, sp.grid, blk, slots, acc);
     }
 }
 
@@ -1421,7 +1429,8 @@ k_dic_backward_rb2(SolverParams sp, RBLayout L, const double *__restrict__ coef,
     const RBForm &f = L.f;
     const int64_t nr = f.nr, h = f.h, H = f.H;
     const double alpha = kUpdate ? st->alpha : 0.0;
-    const Rb2Lane l = rb2_lane(f);
+    const int32_t blk = walk_share(!kUpdate);
+    const Rb2Lane l = rb2_lane(blk, f);
     const int64_t u = l.u, pos = l.pos;
     const int32_t par = l.par;
     const R z = lanes_zero<double, 2>();
@@ -1466,16 +1475,16 @@ k_dic_backward_rb2(SolverParams sp, RBLayout L, const double *__restrict__ coef,
         *reinterpret_cast<typename R::vec *>(w + u) = typename R::vec{wv.v[0], wv.v[1]};
     }
     if (kUpdate) {
-        const double black = part[kPartSumR * sp.grid + blockIdx.x];
+        const double black = part[kPartSumR * sp.grid + blk];
         block_sum<kCellBlock, 2>(acc);
         if (threadIdx.x == 0) {
-            part[kPartWr * sp.grid + blockIdx.x] = acc[0];
-            part[kPartSumR * sp.grid + blockIdx.x] = black + acc[1];
+            part[kPartWr * sp.grid + blk] = acc[0];
+            part[kPartSumR * sp.grid + blk] = black + acc[1];
         }
     } else {
         double a1[1] = {acc[0]};
         const int slots[1] = {kPartWr};
-        write_partials<1>(part, sp.grid, slots, a1);
+        write_partials_at<1>(part, sp.grid, blk, slots, a1);
     }
 }
 
