@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "lf_solver.h"
 
@@ -30,15 +31,16 @@ struct BatchTask {
     const int32_t *patch_type;
     const double *patch_value;
     // problem
-    double *T, *coef, *diagB, *srcB, *r;
-    float *coef32, *diag32, *rD32, *r32, *p32, *q32, *d32;
+    double *T, *coef, *diagB, *srcB;
+    double *bic, *bbc;     // [n_bfaces] boundary coefficients in the order of bface_list
+    float *coef32, *s32, *t32, *r32, *p32, *q32, *d32;
     double *snap;          // [n_steps][n] copies of T after each step (mesh cell order), or null
     const int32_t *iperm;  // mesh cell of each solver row, or null (same order)
     // band layout of the problem's coefficients (nb = 3; 0: sliced row layout)
     const double *band_mag_sf, *band_delta;
     int32_t nb, band_d[kMaxBands];
     double DT, dt, tol, rel_tol, inner_tol;
-    int32_t n, max_iter, max_outer, pad;
+    int32_t n, n_bfaces, max_iter, max_outer;
 };
 
 // tightening of the refinement target, as in the single-problem precision form
@@ -59,71 +61,362 @@ __device__ __forceinline__ void bsum2(double &a0, double &a1) {
     a1 = a[1];
 }
 
+// Rows of a workgroup: thread t takes rows t, t + BS, t + 2 BS, ... in groups
+// of G, whose loads are all issued before the first is used (one problem has
+// only BS / 256 wavefronts per SIMD to hide a load behind).  With so few
+// wavefronts the instructions count too: in an inner group (kIn) every row and
+// every neighbour exists, so that a row's arrays are one uniform base each and
+// the thread's index, with no clamp and no mask; the others (at most the first
+// and the last few of a mesh) read a clamped row and mask it.
+template <int BS, int G, bool kIn>
+struct RowGroup {
+    uint32_t c0;         // the thread's first row of the group
+    int32_t last;        // n - 1
+    __device__ __forceinline__ bool ok(int u) const { return kIn || static_cast<int32_t>(c0) + u * BS <= last; }
+    __device__ __forceinline__ int32_t row(int u) const {
+        const int32_t c = static_cast<int32_t>(c0) + u * BS;
+        return kIn ? c : min(c, last);
+    }
+    // a[row u + off], off uniform
+    template <class T>
+    __device__ __forceinline__ T at(const T *__restrict__ a, int u, int32_t off = 0) const {
+        return kIn ? (a + off + u * BS)[c0] : a[row(u) + off];
+    }
+    template <class T>
+    __device__ __forceinline__ void set(T *__restrict__ a, int u, T v) const {
+        if (kIn) (a + u * BS)[c0] = v;
+        else if (ok(u)) a[row(u)] = v;
+    }
+};
+
+// fn(rows) for the thread's groups in order.  A group is an inner one if all its
+// rows are at least `halo` rows from both ends.
+template <int BS, int G, class Fn>
+__device__ __forceinline__ void each_group(int32_t n, int32_t halo, Fn &&fn) {
+    for (int32_t i = 0; i < n; i += G * BS) {
+        const uint32_t c0 = static_cast<uint32_t>(i) + threadIdx.x;
+        __builtin_assume(c0 < (1u << 28));
+        if (i >= halo && i + G * BS + halo <= n)
+            fn(RowGroup<BS, G, true>{c0, n - 1});
+        else
+            fn(RowGroup<BS, G, false>{c0, n - 1});
+    }
+}
+
+// a b + c, rounded once
+__device__ __forceinline__ float mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the entries of the group's rows in layout_dot's order: coefficients and the
+// neighbours' x.  An entry outside the mesh takes band slot n - 1, which never
+// has a face and holds 0.
+template <int BS, int G, bool kIn, class T>
+__device__ __forceinline__ void group_entries(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g,
+                                              const T *__restrict__ coef, const T *__restrict__ x, T (&a)[G][6],
+                                              T (&xv)[G][6]) {
+    const int32_t n = L.n;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int k = 2 - j;
+            if constexpr (kIn) {
+                a[u][j] = g.at(coef, u, k * n - L.d[k]);
+                xv[u][j] = g.at(x, u, -L.d[k]);
+            } else {
+                const int32_t c = g.row(u), col = c >= L.d[k] ? c - L.d[k] : n - 1;
+                a[u][j] = coef[k * n + col];
+                xv[u][j] = x[col];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            a[u][3 + k] = g.at(coef, u, k * n);
+            if constexpr (kIn) {
+                xv[u][3 + k] = g.at(x, u, L.d[k]);
+            } else {
+                const int32_t c = g.row(u);
+                xv[u][3 + k] = x[c < n - L.d[k] ? c + L.d[k] : c];
+            }
+        }
+    }
+}
+
+// y = acc + sum of the rows' entries
+template <int BS, int G, bool kIn, class T>
+__device__ __forceinline__ void group_dot(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g,
+                                          const T *__restrict__ coef, const T *__restrict__ x, const T (&acc)[G],
+                                          T (&y)[G]) {
+    T a[G][6], xv[G][6];
+    group_entries(L, g, coef, x, a, xv);
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        y[u] = acc[u];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) y[u] = mul_add(a[u][j], xv[u][j], y[u]);
+    }
+}
+
+template <int BS, int G, bool kIn, class T>
+__device__ __forceinline__ void group_dot(const SellLayout &L, const RowGroup<BS, G, kIn> &g,
+                                          const T *__restrict__ coef, const T *__restrict__ x, const T (&acc)[G],
+                                          T (&y)[G]) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) y[u] = layout_dot(L, g.row(u), coef, x, acc[u]);
+}
+
+// Assembly of the group's rows: lap_diag, and y = sum a_j x_j, sa = sum a_j of
+// the row's off-diagonal entries; the coefficients are stored.
+template <int BS, int G, bool kIn>
+__device__ __forceinline__ void group_assemble(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g, double DT,
+                                               const double *__restrict__ x, double *__restrict__ coef,
+                                               double (&lap)[G], double (&a)[G][6], double (&xv)[G][6]) {
+    double dl[G][6];
+    group_entries(L, g, L.mag_sf, x, a, xv);
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int k = 2 - j;
+            if constexpr (kIn) {
+                dl[u][j] = g.at(L.delta, u, k * L.n - L.d[k]);
+            } else {
+                const int32_t c = g.row(u);
+                dl[u][j] = L.delta[k * L.n + (c >= L.d[k] ? c - L.d[k] : L.n - 1)];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) dl[u][3 + k] = g.at(L.delta, u, k * L.n);
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        lap[u] = 0.0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const double up = dl[u][j] * (DT * a[u][j]);
+            a[u][j] = -up;
+            lap[u] -= up;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g.set(coef + k * L.n, u, a[u][3 + k]);
+    }
+}
+
+// FP32 coefficients of the scaled matrix, a_cn t_c t_n, of the group's rows
+template <int BS, int G, bool kIn>
+__device__ __forceinline__ void group_scale(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g,
+                                            const float *__restrict__ t32, const double *__restrict__ coef,
+                                            float *__restrict__ coef32) {
+    double a[G][3];
+    float tc[G], tn[G][3];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        tc[u] = g.at(t32, u);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            a[u][k] = g.at(coef, u, k * L.n);
+            if constexpr (kIn) {
+                tn[u][k] = g.at(t32, u, L.d[k]);
+            } else {
+                const int32_t c = g.row(u);
+                tn[u][k] = t32[c < L.n - L.d[k] ? c + L.d[k] : c];     // a slot without a face holds 0
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            g.set(coef32 + k * L.n, u,
+                  static_cast<float>(a[u][k] * (static_cast<double>(tc[u]) * static_cast<double>(tn[u][k]))));
+}
+
+template <int BS, int G, bool kIn>
+__device__ __forceinline__ void group_scale(const SellLayout &L, const RowGroup<BS, G, kIn> &g,
+                                            const float *__restrict__ t32, const double *__restrict__ coef,
+                                            float *__restrict__ coef32) {
+    for (int u = 0; u < G; ++u) {
+        if (!g.ok(u)) continue;
+        const int32_t c = g.row(u), len = L.mr.rlen[c];
+        const double tc = t32[c];
+        int32_t idx = row_base(L.mr, c);
+        for (int32_t j = 0; j < len; ++j, idx += kSlice)
+            coef32[idx] = static_cast<float>(coef[idx] * (tc * static_cast<double>(t32[L.mr.scol[idx]])));
+    }
+}
+
+// One problem's steps.  The inner FP32 solve is the precision form's: CG on the
+// matrix scaled to unit diagonal (t = 1/sqrt(diagB) rounded to FP32, As =
+// t A t, rs = t r, d = t y), whose iterates are those of the diagonally
+// preconditioned CG of A d = r; it stops on the L1 norm of A's residual,
+// sum s|rs| with s = sqrt(diagB).
+//
+// What bounds it is what one workgroup's CU can fetch past its L1: 32 bytes per
+// clock, 75 GB/s, whatever level answers (the 68 bytes per row of an inner
+// iteration on memory-resident vectors took 50 us at 32^3).  So the inner
+// vectors live in the LDS, as many of p (which the neighbours read too), r, q
+// and y as it holds (kLds of them, from the problem's size alone), and the
+// start of a pass (rs, its sums) is formed where the FP64 residual is.  A
+// vector kept in memory takes the same rows in the same order with the same
+// expressions, so its place does not change a bit.
+//
 // The task's arrays are distinct allocations: taking them into __restrict__
 // locals lets the compiler overlap the loads of several rows of a loop.
-template <int BS, class Lay>
-__device__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps, lf_solve_stats *__restrict__ stats) {
+template <int BS, int kLds, class Lay>
+__device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps,
+                                           lf_solve_stats *__restrict__ stats, float *lds) {
     const int32_t n = tk.n;
-    const double *__restrict__ V = tk.V;
-    const int32_t *__restrict__ bface_start = tk.bface_start;
-    const int32_t *__restrict__ bface_list = tk.bface_list;
-    const int32_t *__restrict__ bface_patch = tk.bface_patch;
-    const double *__restrict__ bmag_sf = tk.bmag_sf;
-    const double *__restrict__ bdelta = tk.bdelta;
-    const int32_t *__restrict__ patch_type = tk.patch_type;
-    const double *__restrict__ patch_value = tk.patch_value;
-    double *__restrict__ T = tk.T;
-    double *__restrict__ coef = tk.coef;
-    double *__restrict__ diagB = tk.diagB;
-    double *__restrict__ srcB = tk.srcB;
-    double *__restrict__ r = tk.r;
-    float *__restrict__ coef32 = tk.coef32;
-    float *__restrict__ diag32 = tk.diag32;
-    float *__restrict__ rD32 = tk.rD32;
-    float *__restrict__ r32 = tk.r32;
-    float *__restrict__ p32 = tk.p32;
-    float *__restrict__ q32 = tk.q32;
-    float *__restrict__ d32 = tk.d32;
+    const double *__restrict__ V = as_global(tk.V);
+    const int32_t *__restrict__ bface_start = as_global(tk.bface_start);
+    const int32_t *__restrict__ bface_list = as_global(tk.bface_list);
+    double *__restrict__ T = as_global(tk.T);
+    double *__restrict__ coef = as_global(tk.coef);
+    double *__restrict__ diagB = as_global(tk.diagB);
+    double *__restrict__ srcB = as_global(tk.srcB);
+    double *__restrict__ ic = as_global(tk.bic);
+    double *__restrict__ bc = as_global(tk.bbc);
+    float *__restrict__ coef32 = as_global(tk.coef32);
+    float *__restrict__ s32 = as_global(tk.s32);
+    float *__restrict__ t32 = as_global(tk.t32);
+    float *__restrict__ p = kLds > 0 ? lds : as_global(tk.p32);
+    float *__restrict__ r32 = kLds > 1 ? lds + n : as_global(tk.r32);
+    float *__restrict__ q32 = kLds > 2 ? lds + 2 * n : as_global(tk.q32);
+    float *__restrict__ d32 = kLds > 3 ? lds + 3 * n : as_global(tk.d32);
+    const int32_t *__restrict__ bface_patch = as_global(tk.bface_patch);
+    const int32_t *__restrict__ patch_type = as_global(tk.patch_type);
+    const double *__restrict__ patch_value = as_global(tk.patch_value);
+    const double *__restrict__ bmag_sf = as_global(tk.bmag_sf);
+    const double *__restrict__ bdelta = as_global(tk.bdelta);
     const int32_t tid = static_cast<int32_t>(threadIdx.x);
     const double rdt = 1.0 / tk.dt;
     const double DT = tk.DT;
+    // Rows of a group, per phase.  A load that misses the L1 comes back after
+    // about a microsecond and the next group's loads are not issued before: as
+    // many rows as the registers (131072 / BS per thread) hold loads for, in
+    // the FP32 vector updates (kG), the FP32 product (kGP), the FP64 product
+    // (kG64) and the assembly (kGA).
+    constexpr int kG = BS == 1024 ? 8 : 16, kGP = BS == 1024 ? 4 : 8;
+    constexpr int kG64 = BS == 1024 ? 2 : 4, kGA = BS == 1024 ? 1 : 4;
+    constexpr bool kBand = !std::is_same_v<Lay, SellLayout>;
+    int32_t halo = n;                 // rows between a row and its farthest neighbour (rows: unknown)
+    if constexpr (kBand) halo = L.d[2];
+    // sum of x0 = T; the later steps' is taken with the last residual
+    double sx = 0.0;
+    each_group<BS, kG>(n, 0, [&](const auto &g) {
+        double x[kG];
+#pragma unroll
+        for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
+#pragma unroll
+        for (int u = 0; u < kG; ++u) sx += g.ok(u) ? x[u] : 0.0;
+    });
+    // boundary coefficients, in the order in which a row reads its faces'
+    for (int32_t i = tid; i < tk.n_bfaces; i += BS) {
+        const int32_t b = bface_list[i];
+        const int32_t pt = bface_patch[b];
+        const bool fixed = patch_type[pt] == LF_BC_FIXED_VALUE;
+        const double f = DT * bmag_sf[b], dl = bdelta[b];
+        ic[i] = fixed ? f * dl : 0.0;
+        bc[i] = fixed ? f * (dl * patch_value[pt]) : 0.0;
+    }
+    sx = bsum1<BS>(sx);
     for (int32_t step = 0; step < n_steps; ++step) {
-        // ---- mean of x0 = T
-        double sx = 0.0;
-        for (int32_t c = tid; c < n; c += BS) sx += T[c];
-        const double x_avg = bsum1<BS>(sx) / static_cast<double>(n);
-        // ---- assembly (FP64 + FP32 copy), r0 = b - A x0, normalisation terms
+        const double x_avg = sx / static_cast<double>(n);
+        // ---- assembly (FP64), r0 = b - A x0, normalisation terms
         double a_r = 0.0, a_nf = 0.0;
-        for (int32_t c = tid; c < n; c += BS) {
-            RowCoefs<Lay> rcf;
-            const double lap_diag = assemble_coefs<false>(L, c, DT, coef, nullptr, rcf);
-            store_coef32(L, c, coef, rcf, coef32);
-            const double v = V[c];
-            const double xc = T[c];
-            double db = rdt * v - lap_diag;
-            double sb = (rdt * xc) * v;
-            for (int32_t i = bface_start[c]; i < bface_start[c + 1]; ++i) {
-                const int32_t b = bface_list[i];
-                const int32_t pt = bface_patch[b];
-                if (patch_type[pt] == LF_BC_FIXED_VALUE) {
-                    const double g = DT * bmag_sf[b];
-                    db += g * bdelta[b];
-                    sb += g * (bdelta[b] * patch_value[pt]);
-                }
-            }
+        // the start of a refinement pass from a row's FP64 residual: rs, which is
+        // the first direction too, y = 0, and the terms of sum s|rs| and rs.rs
+        double s_r = 0.0, s_wr = 0.0;
+        auto start_row = [&](int32_t c, double rc, float s, float t) {
+            const float rs = static_cast<float>(rc * static_cast<double>(t));
+            s_r = mul_add(static_cast<double>(s), fabs(static_cast<double>(rs)), s_r);
+            s_wr = mul_add(static_cast<double>(rs), static_cast<double>(rs), s_wr);
+            p[c] = rs;
+            r32[c] = rs;
+            d32[c] = 0.0f;
+        };
+        // one row from its off-diagonal entries: off(ax, sa) adds sum a_j x_j
+        // and sum a_j in entry order
+        auto finish_row = [&](int32_t c, double v, double xc, double lap_diag, double bd, double bs, auto &&off) {
+            const double db = (rdt * v - lap_diag) + bd, sb = (rdt * xc) * v + bs;
             diagB[c] = db;
             srcB[c] = sb;
-            diag32[c] = static_cast<float>(db);
-            rD32[c] = static_cast<float>(1.0 / db);
+            const double s = sqrt(db);
+            const float sf = static_cast<float>(s), tf = static_cast<float>(1.0 / s);
+            s32[c] = sf;
+            t32[c] = tf;
             double ax = db * xc, sa = db;
-            row_amul_sum(L, c, coef, rcf, T, ax, sa);
+            off(ax, sa);
             const double rc = sb - ax;
-            r[c] = rc;
+            start_row(c, rc, sf, tf);
             const double pa = sa * x_avg;
             a_r += fabs(rc);
             a_nf += fabs(ax - pa) + fabs(sb - pa);
+        };
+        if constexpr (kBand) {
+            each_group<BS, kGA>(n, halo, [&](const auto &g) {
+                double a[kGA][6], xv[kGA][6], lap[kGA], v[kGA], xc[kGA], bd[kGA], bs[kGA];
+                int32_t b0[kGA], b1[kGA];
+#pragma unroll
+                for (int u = 0; u < kGA; ++u) {
+                    b0[u] = g.at(bface_start, u);
+                    b1[u] = g.at(bface_start, u, 1);
+                    v[u] = g.at(V, u);
+                    xc[u] = g.at(T, u);
+                }
+                group_assemble(L, g, DT, T, coef, lap, a, xv);
+                // the rows' boundary faces side by side: one load's wait for all
+#pragma unroll
+                for (int u = 0; u < kGA; ++u) bd[u] = bs[u] = 0.0;
+                for (int32_t t = 0;; ++t) {
+                    bool more = false;
+                    double di[kGA], si[kGA];
+#pragma unroll
+                    for (int u = 0; u < kGA; ++u) {
+                        const bool has = b0[u] + t < b1[u];
+                        more = more || has;
+                        di[u] = has ? ic[b0[u] + t] : 0.0;
+                        si[u] = has ? bc[b0[u] + t] : 0.0;
+                    }
+                    if (!more) break;
+#pragma unroll
+                    for (int u = 0; u < kGA; ++u) {
+                        bd[u] += di[u];
+                        bs[u] += si[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kGA; ++u)
+                    if (g.ok(u))
+                        finish_row(g.row(u), v[u], xc[u], lap[u], bd[u], bs[u], [&](double &ax, double &sa) {
+#pragma unroll
+                            for (int j = 0; j < 6; ++j) {
+                                ax += a[u][j] * xv[u][j];
+                                sa += a[u][j];
+                            }
+                        });
+            });
+        } else {
+            for (int32_t c = tid; c < n; c += BS) {
+                RowCoefs<Lay> rcf;
+                const double lap_diag = assemble_coefs<false>(L, c, DT, coef, nullptr, rcf);
+                double bd = 0.0, bs = 0.0;
+                for (int32_t i = bface_start[c]; i < bface_start[c + 1]; ++i) {
+                    bd += ic[i];
+                    bs += bc[i];
+                }
+                finish_row(c, V[c], T[c], lap_diag, bd, bs,
+                           [&](double &ax, double &sa) { row_amul_sum(L, c, coef, rcf, T, ax, sa); });
+            }
         }
-        bsum2<BS>(a_r, a_nf);
+        {
+            double a[4] = {a_r, a_nf, s_r, s_wr};
+            block_sum<BS, 4>(a);
+            a_r = a[0];
+            a_nf = a[1];
+            s_r = a[2];
+            s_wr = a[3];
+        }
+        each_group<BS, kG64>(n, halo, [&](const auto &g) { group_scale(L, g, t32, coef, coef32); });
         const double nf = a_nf + 1e-20;
         const double res0 = a_r / nf;
         double res = res0;
@@ -133,52 +426,69 @@ __device__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps, l
         bool tight = check_conv(res0, res0, kBatchTighten * tk.tol, kBatchTighten * tk.rel_tol);
         // ---- refinement passes
         while (!nonfinite && !tight && n_outer < tk.max_outer && n_iter < tk.max_iter) {
-            double s_r = 0.0, s_wr = 0.0;
-            #pragma unroll 2
-            for (int32_t c = tid; c < n; c += BS) {
-                const float rc = static_cast<float>(r[c]);
-                r32[c] = rc;
-                d32[c] = 0.0f;
-                const float wc = rD32[c] * rc;
-                s_r += fabs(static_cast<double>(rc));
-                s_wr += static_cast<double>(wc) * static_cast<double>(rc);
-            }
-            bsum2<BS>(s_r, s_wr);
+            __syncthreads();          // coef32 of the first pass, p of every pass
             const double target = fmax(tk.inner_tol * s_r, 0.5 * kBatchTighten * tk.tol * nf);
             double wArA = s_wr;
             double beta = 0.0;
             bool inner_done = (s_r <= target) || !(s_wr > 0.0);
             int32_t inner_iter = 0;
             while (!inner_done) {
-                const float fb = static_cast<float>(beta);
-                #pragma unroll 2
-                for (int32_t c = tid; c < n; c += BS) {
-                    const float wc = rD32[c] * r32[c];
-                    p32[c] = inner_iter == 0 ? wc : wc + fb * p32[c];
+                if (inner_iter > 0) {          // p = rs in the first iteration
+                    const float fb = static_cast<float>(beta);
+                    each_group<BS, kG>(n, 0, [&](const auto &g) {
+                        float rs[kG], pc[kG];
+#pragma unroll
+                        for (int u = 0; u < kG; ++u) {
+                            rs[u] = g.at(r32, u);
+                            pc[u] = g.at(p, u);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kG; ++u) g.set(p, u, mul_add(fb, pc[u], rs[u]));
+                    });
+                    __syncthreads();
                 }
-                __syncthreads();
                 double s_pq = 0.0;
-                for (int32_t c = tid; c < n; c += BS) {
-                    const float pc = p32[c];
-                    const float qc = layout_dot(L, c, coef32, p32, diag32[c] * pc);
-                    q32[c] = qc;
-                    s_pq += static_cast<double>(qc) * static_cast<double>(pc);
-                }
+                each_group<BS, kGP>(n, halo, [&](const auto &g) {
+                    float pc[kGP], qc[kGP];
+#pragma unroll
+                    for (int u = 0; u < kGP; ++u) pc[u] = g.at(p, u);
+                    group_dot(L, g, coef32, p, pc, qc);
+#pragma unroll
+                    for (int u = 0; u < kGP; ++u) {
+                        const float q = g.ok(u) ? qc[u] : 0.0f;
+                        g.set(q32, u, q);
+                        s_pq = mul_add(static_cast<double>(q), static_cast<double>(pc[u]), s_pq);
+                    }
+                });
                 const double pq = bsum1<BS>(s_pq);
                 if (!isfinite(pq)) { nonfinite = true; break; }
                 if (!(fabs(pq) > 0.0)) break;
                 const double alpha = wArA / pq;
                 const float fa = static_cast<float>(alpha);
                 double u_r = 0.0, u_wr = 0.0;
-                #pragma unroll 2
-                for (int32_t c = tid; c < n; c += BS) {
-                    d32[c] += fa * p32[c];
-                    const float rc = r32[c] - fa * q32[c];
-                    r32[c] = rc;
-                    const float wc = rD32[c] * rc;
-                    u_r += fabs(static_cast<double>(rc));
-                    u_wr += static_cast<double>(wc) * static_cast<double>(rc);
-                }
+                each_group<BS, kG>(n, 0, [&](const auto &g) {
+                    float sc[kG], pc[kG], rs[kG], q[kG], y[kG];
+#pragma unroll
+                    for (int u = 0; u < kG; ++u) {
+                        sc[u] = g.at(s32, u);
+                        pc[u] = g.at(p, u);
+                        q[u] = g.at(q32, u);
+                        rs[u] = g.at(r32, u);
+                        y[u] = g.at(d32, u);
+                    }
+#pragma unroll
+                    for (int u = 0; u < kG; ++u) {
+                        rs[u] = mul_add(-fa, q[u], rs[u]);
+                        g.set(r32, u, rs[u]);
+                        g.set(d32, u, mul_add(fa, pc[u], y[u]));
+                    }
+#pragma unroll
+                    for (int u = 0; u < kG; ++u) {
+                        const double rd = g.ok(u) ? static_cast<double>(rs[u]) : 0.0;
+                        u_r = mul_add(static_cast<double>(sc[u]), fabs(rd), u_r);
+                        u_wr = mul_add(rd, rd, u_wr);
+                    }
+                });
                 bsum2<BS>(u_r, u_wr);
                 ++inner_iter;
                 ++n_iter;
@@ -191,18 +501,55 @@ __device__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps, l
                 }
             }
             if (nonfinite) break;
-            // T += d, then the FP64 true residual
-            #pragma unroll 2
-            for (int32_t c = tid; c < n; c += BS) T[c] += static_cast<double>(d32[c]);
+            // T += d, then the FP64 true residual (and the sum of T)
+            each_group<BS, kG>(n, 0, [&](const auto &g) {
+                double x[kG];
+                float tc[kG], y[kG];
+#pragma unroll
+                for (int u = 0; u < kG; ++u) {
+                    y[u] = g.at(d32, u);
+                    x[u] = g.at(T, u);
+                    tc[u] = g.at(t32, u);
+                }
+#pragma unroll
+                for (int u = 0; u < kG; ++u)
+                    g.set(T, u, x[u] + static_cast<double>(y[u]) * static_cast<double>(tc[u]));
+            });
             __syncthreads();
-            double o_r = 0.0;
-            for (int32_t c = tid; c < n; c += BS) {
-                const double ax = layout_dot(L, c, coef, T, diagB[c] * T[c]);
-                const double rc = srcB[c] - ax;
-                r[c] = rc;
-                o_r += fabs(rc);
+            double o_r = 0.0, o_x = 0.0;
+            s_r = s_wr = 0.0;
+            each_group<BS, kG64>(n, halo, [&](const auto &g) {
+                double xc[kG64], ax[kG64], b[kG64], y[kG64];
+                float sc[kG64], tc[kG64];
+#pragma unroll
+                for (int u = 0; u < kG64; ++u) {
+                    xc[u] = g.at(T, u);
+                    ax[u] = g.at(diagB, u);
+                    b[u] = g.at(srcB, u);
+                    sc[u] = g.at(s32, u);
+                    tc[u] = g.at(t32, u);
+                }
+#pragma unroll
+                for (int u = 0; u < kG64; ++u) ax[u] *= xc[u];
+                group_dot(L, g, coef, T, ax, y);
+#pragma unroll
+                for (int u = 0; u < kG64; ++u) {
+                    if (!g.ok(u)) continue;
+                    const double rc = b[u] - y[u];
+                    start_row(g.row(u), rc, sc[u], tc[u]);
+                    o_r += fabs(rc);
+                    o_x += xc[u];
+                }
+            });
+            {
+                double a[4] = {o_r, o_x, s_r, s_wr};
+                block_sum<BS, 4>(a);
+                o_r = a[0];
+                o_x = a[1];
+                s_r = a[2];
+                s_wr = a[3];
             }
-            o_r = bsum1<BS>(o_r);
+            sx = o_x;
             res = o_r / nf;
             ++n_outer;
             nonfinite = !isfinite(res);
@@ -210,10 +557,16 @@ __device__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps, l
             tight = check_conv(res, res0, kBatchTighten * tk.tol, kBatchTighten * tk.rel_tol);
         }
         if (tk.snap) {
-            double *__restrict__ out = tk.snap + static_cast<int64_t>(step) * n;
-            const int32_t *__restrict__ ip = tk.iperm;
-            #pragma unroll 2
-            for (int32_t c = tid; c < n; c += BS) out[ip ? ip[c] : c] = T[c];
+            double *__restrict__ out = as_global(tk.snap) + static_cast<int64_t>(step) * n;
+            const int32_t *__restrict__ ip = as_global(tk.iperm);
+            each_group<BS, kG>(n, 0, [&](const auto &g) {
+                double x[kG];
+#pragma unroll
+                for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
+#pragma unroll
+                for (int u = 0; u < kG; ++u)
+                    if (g.ok(u)) out[ip ? ip[g.row(u)] : g.row(u)] = x[u];
+            });
         }
         if (tid == 0) {
             lf_solve_stats st;
@@ -241,10 +594,18 @@ __device__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps, l
     }
 }
 
+// LDS vectors of a problem of n rows in the band layout: as many of the four as
+// fit
+__host__ __device__ inline int lds_vectors(int32_t n) {
+    constexpr int32_t kRows = 39 * 1024;     // 156 KiB of the CU's 160; the rest is for the sums
+    return n > kRows ? 0 : kRows / n < 4 ? kRows / n : 4;
+}
+
 template <int BS>
 __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ tasks, int32_t n_tasks,
                                              int32_t *__restrict__ counter, int32_t n_steps,
                                              lf_solve_stats *__restrict__ stats) {
+    extern __shared__ float lds[];
     __shared__ int32_t s_task;
     for (;;) {
         if (threadIdx.x == 0) s_task = atomicAdd(counter, 1);
@@ -259,13 +620,21 @@ __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ task
             L.n = tk.n;
 #pragma unroll
             for (int k = 0; k < 3; ++k) L.d[k] = tk.band_d[k];
-            L.mag_sf = tk.band_mag_sf;
-            L.delta = tk.band_delta;
-            solve_task<BS>(tk, L, n_steps, st);
+            L.mag_sf = as_global(tk.band_mag_sf);
+            L.delta = as_global(tk.band_delta);
+            switch (lds_vectors(tk.n)) {
+                case 0: solve_task<BS, 0>(tk, L, n_steps, st, nullptr); break;
+                case 1: solve_task<BS, 1>(tk, L, n_steps, st, lds); break;
+                case 2: solve_task<BS, 2>(tk, L, n_steps, st, lds); break;
+                case 3: solve_task<BS, 3>(tk, L, n_steps, st, lds); break;
+                default: solve_task<BS, 4>(tk, L, n_steps, st, lds); break;
+            }
         } else {
-            const SellLayout L{MeshRows{tk.soff, tk.scol, tk.sface, tk.rlen}, tk.mag_sf, tk.delta, tk.emag_sf,
-                               tk.edelta};
-            solve_task<BS>(tk, L, n_steps, st);
+            const SellLayout L{MeshRows{as_global(tk.soff), as_global(tk.scol), as_global(tk.sface),
+                                        as_global(tk.rlen)},
+                               as_global(tk.mag_sf), as_global(tk.delta), as_global(tk.emag_sf),
+                               as_global(tk.edelta)};
+            solve_task<BS, 0>(tk, L, n_steps, st, nullptr);
         }
     }
 }
@@ -289,6 +658,19 @@ struct lf_batch {
     bool in_flight = false;
     int device = 0;
 };
+
+// the kernel with the LDS of the launch's largest need (above 64 KiB it has to
+// be allowed first)
+template <int BS>
+static lf_status launch_batch(int32_t lds_rows, int32_t grid, int32_t n, int32_t n_steps, lf_batch *b, hipStream_t s) {
+    const int lds = static_cast<int>(sizeof(float)) * lds_rows;
+    if (lds > (48 << 10))
+        LF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<BS>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, 156 << 10));
+    hipLaunchKernelGGL(k_batch<BS>, dim3(static_cast<unsigned>(grid)), dim3(BS), static_cast<unsigned>(lds), s,
+                       b->d_tasks, n, b->d_counter, n_steps, b->d_stats);
+    return LF_OK;
+}
 
 static void carve_batch(Carver &cv, int32_t max_tasks, int32_t max_steps, lf_batch *b) {
     auto *tasks = cv.take<BatchTask>(static_cast<size_t>(max_tasks));
@@ -376,6 +758,7 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
             return LF_EINVAL;
         }
     }
+    int32_t lds_rows = 0;     // the launch's LDS, in floats
     for (int32_t i = 0; i < n; ++i) {
         const lf_problem *P = problems[i];
         if (!P) { set_error("problem %d is NULL", i); return LF_EINVAL; }
@@ -398,8 +781,9 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         t.iperm = m->iperm;
         t.bmag_sf = m->bmag_sf; t.bdelta = m->bdelta;
         t.patch_type = P->patch_type; t.patch_value = P->patch_value;
-        t.T = P->T; t.coef = P->coef; t.diagB = P->diagB; t.srcB = P->srcB; t.r = P->r;
-        t.coef32 = P->coef32; t.diag32 = P->diag32; t.rD32 = P->rD32; t.r32 = P->r32;
+        t.T = P->T; t.coef = P->coef; t.diagB = P->diagB; t.srcB = P->srcB;
+        t.bic = P->bic; t.bbc = P->bbc;
+        t.coef32 = P->coef32; t.s32 = P->diag32; t.t32 = P->rD32; t.r32 = P->r32;
         t.p32 = P->p32; t.q32 = P->q32; t.d32 = P->d32;
         t.snap = snapshots ? snapshots[i] : nullptr;
         if (P->banded && m->n_bands != 3) {
@@ -412,7 +796,9 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         t.band_mag_sf = m->band_mag_sf;
         t.band_delta = m->band_delta;
         t.DT = P->DT; t.dt = P->dt; t.tol = P->sp.tol; t.rel_tol = P->sp.rel_tol; t.inner_tol = P->sp.inner_tol;
-        t.n = m->N; t.max_iter = P->sp.max_iter; t.max_outer = P->sp.max_outer; t.pad = 0;
+        t.n = m->N; t.max_iter = P->sp.max_iter; t.max_outer = P->sp.max_outer;
+        t.n_bfaces = m->B;
+        if (t.nb == 3) lds_rows = std::max(lds_rows, lds_vectors(t.n) * t.n);
     }
     hipStream_t s = b->stream;
     int32_t g = n_workgroups > 0 ? std::min(n_workgroups, n) : n;
@@ -420,9 +806,9 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
     hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, s, b->d_counter);
     LF_HIP(hipEventRecord(b->start, s));
     switch (block_threads) {
-        case 256: hipLaunchKernelGGL(k_batch<256>, dim3(g), dim3(256), 0, s, b->d_tasks, n, b->d_counter, n_steps, b->d_stats); break;
-        case 512: hipLaunchKernelGGL(k_batch<512>, dim3(g), dim3(512), 0, s, b->d_tasks, n, b->d_counter, n_steps, b->d_stats); break;
-        default: hipLaunchKernelGGL(k_batch<1024>, dim3(g), dim3(1024), 0, s, b->d_tasks, n, b->d_counter, n_steps, b->d_stats); break;
+        case 256: LF_TRY(launch_batch<256>(lds_rows, g, n, n_steps, b, s)); break;
+        case 512: LF_TRY(launch_batch<512>(lds_rows, g, n, n_steps, b, s)); break;
+        default: LF_TRY(launch_batch<1024>(lds_rows, g, n, n_steps, b, s)); break;
     }
     LF_HIP(hipGetLastError());
     LF_HIP(hipMemcpyAsync(b->h_stats, b->d_stats, sizeof(lf_solve_stats) * static_cast<size_t>(n) * n_steps,

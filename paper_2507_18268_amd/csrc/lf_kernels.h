@@ -9,6 +9,16 @@
 
 namespace lf {
 
+// A pointer that was read from device memory (a task or member table), as one to
+// global memory.  The compiler knows that only of kernel arguments; through any
+// other pointer it issues flat accesses, which also occupy the LDS path and
+// wait for both (through an integer: the round trip between pointer types
+// alone is folded away).
+template <class T>
+__device__ __forceinline__ T *as_global(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)reinterpret_cast<uintptr_t>(p);
+}
+
 // Sum over a wavefront of 64 lanes by xor butterflies; every lane ends with the
 // same value because each pairwise sum is commutative.
 __device__ __forceinline__ double wave_sum(double v) {

@@ -52,7 +52,10 @@ void carve_mixed(Carver &cv, const lf_mesh *m, bool banded, lf_problem *P) {
     auto *coef32 = cv.take<float>(coef_slots(m, banded));
     float *v32[7];
     for (auto &v : v32) v = cv.take<float>(N);
+    auto *bic = cv.take<double>(m->B);
+    auto *bbc = cv.take<double>(m->B);
     if (P) {
+        P->bic = bic; P->bbc = bbc;
         P->coef32 = coef32; P->diag32 = v32[0]; P->rD32 = v32[1]; P->r32 = v32[2];
         P->p32 = v32[3]; P->q32 = v32[4]; P->d32 = v32[5]; P->sig32 = v32[6];
     }

@@ -180,6 +180,7 @@ struct lf_problem {
     // mixed precision (FP32 inner solve)
     float *coef32 = nullptr, *diag32 = nullptr, *rD32 = nullptr;
     float *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr;
+    double *bic = nullptr, *bbc = nullptr;     // [B] batched kernel: boundary coefficients by boundary list position
     float *sig32 = nullptr;                    // multi-kernel precision form: sqrt(diagB) in FP32
     // host side
     lf::PcgState *h_state = nullptr;           // pinned
