@@ -340,8 +340,8 @@ lf_status lf_problem_layout(const lf_problem *problem, int32_t *layout);
  * red-black pairs per lane (16-byte loads), under the same rule as the row
  * walk.
  * 4: form 2, and the FP64 solve with the diagonal preconditioner, where its
- * iteration's reductions are not folded into the update and direction (more
- * than 512 partials per slot), runs CG on the Jacobi-scaled system
+ * kernels write more than 512 partials per slot, runs CG on the Jacobi-scaled
+ * system
  * S A S y = S b, S = diag(1/sqrt(diagB)) (unit diagonal; the same iterates as
  * the diagonally preconditioned CG of A in exact arithmetic, with the
  * residual norm still taken of b - A x): the iteration's product reads no
@@ -532,7 +532,9 @@ lf_status lf_group_poll(lf_group *group, lf_problem **finished, int32_t max_fini
 #define LF_K_SETUP1 1        /* partial sums of x0 (mean for the normalisation) */
 #define LF_K_COMMIT 2        /* last pending x += alpha p of a solve */
 #define LF_K_DIRECTION 3     /* p = w + beta p, deferred x += alpha p */
-#define LF_K_AMUL_DOT 4      /* q = A p, p.q partials */
+#define LF_K_AMUL_DOT 4      /* q = A p, p.q partials; FP64 diagonal solves of up to
+                                2 M rows: the direction update is part of it, and
+                                the reductions of it and of the update */
 #define LF_K_UPDATE 5        /* r -= alpha q, |r| and w.r partials */
 #define LF_K_DIC_RD 6        /* DIC diagonal */
 #define LF_K_DIC_FORWARD 7   /* DIC forward sweep (black rows) */

@@ -218,12 +218,23 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
             }
         }
     }
-    P->fold = opts.precision == LF_PREC_FP64 && opts.precond == LF_PC_DIAGONAL && !P->rb &&
-              P->sp.grid_amul <= kFoldPartials && P->sp.grid_upd <= kFoldPartials;
+    // FP64 diagonal solves without a walk, up to kFoldMaxRows rows: two launches
+    // per iteration.  Their partials per slot stay at most 2048, which every
+    // workgroup sums (4 per thread): one row per thread while that holds
+    // (more workgroups), then kFoldRows in the product and kUpdRows in the update.
+    const bool fp64_diag = opts.precision == LF_PREC_FP64 && opts.precond == LF_PC_DIAGONAL && !P->rb;
+    P->fold = fp64_diag && !P->walk && m->N <= kFoldMaxRows;
+    if (P->fold) {
+        P->sp.grid_amul = m->N <= kFoldOneRow ? P->sp.grid : fold_blocks(m->N);
+        P->sp.grid_upd = m->N <= kFoldOneRow ? P->sp.grid : update_blocks(m->N);
+        P->sp.grid_sum = update_blocks(m->N);
+        P->sp.by_die = m->N <= kFoldDieRows ? 1 : 0;
+    }
     // larger diagonal FP64 solves on the block walk iterate on the Jacobi-scaled
     // matrix (its coefficients carved by carve_problem for every FP64 diagonal
-    // problem of a three-band layout)
-    P->scaled = P->box && !P->fold && opts.precision == LF_PREC_FP64 && opts.precond == LF_PC_DIAGONAL;
+    // problem of a three-band layout); not the small ones (512 partials per
+    // slot), where the scaling's pass costs more than it saves
+    P->scaled = P->box && fp64_diag && (P->sp.grid_amul > kScaledPartials || P->sp.grid_upd > kScaledPartials);
     P->sp.max_outer = opts.max_outer > 0 ? opts.max_outer : 50;
     P->sp.inner_tol = opts.inner_tol > 0.0 ? opts.inner_tol : 1e-5;
     P->sp.inner_restart = opts.inner_restart ? 1 : 0;

@@ -61,34 +61,6 @@ __device__ __forceinline__ void bsum2(double &a0, double &a1) {
     a1 = a[1];
 }
 
-// Rows of a workgroup: thread t takes rows t, t + BS, t + 2 BS, ... in groups
-// of G, whose loads are all issued before the first is used (one problem has
-// only BS / 256 wavefronts per SIMD to hide a load behind).  With so few
-// wavefronts the instructions count too: in an inner group (kIn) every row and
-// every neighbour exists, so that a row's arrays are one uniform base each and
-// the thread's index, with no clamp and no mask; the others (at most the first
-// and the last few of a mesh) read a clamped row and mask it.
-template <int BS, int G, bool kIn>
-struct RowGroup {
-    uint32_t c0;         // the thread's first row of the group
-    int32_t last;        // n - 1
-    __device__ __forceinline__ bool ok(int u) const { return kIn || static_cast<int32_t>(c0) + u * BS <= last; }
-    __device__ __forceinline__ int32_t row(int u) const {
-        const int32_t c = static_cast<int32_t>(c0) + u * BS;
-        return kIn ? c : min(c, last);
-    }
-    // a[row u + off], off uniform
-    template <class T>
-    __device__ __forceinline__ T at(const T *__restrict__ a, int u, int32_t off = 0) const {
-        return kIn ? (a + off + u * BS)[c0] : a[row(u) + off];
-    }
-    template <class T>
-    __device__ __forceinline__ void set(T *__restrict__ a, int u, T v) const {
-        if (kIn) (a + u * BS)[c0] = v;
-        else if (ok(u)) a[row(u)] = v;
-    }
-};
-
 // fn(rows) for the thread's groups in order.  A group is an inner one if all its
 // rows are at least `halo` rows from both ends.
 template <int BS, int G, class Fn>
@@ -103,52 +75,13 @@ __device__ __forceinline__ void each_group(int32_t n, int32_t halo, Fn &&fn) {
     }
 }
 
-// a b + c, rounded once
-__device__ __forceinline__ float mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// the entries of the group's rows in layout_dot's order: coefficients and the
-// neighbours' x.  An entry outside the mesh takes band slot n - 1, which never
-// has a face and holds 0.
-template <int BS, int G, bool kIn, class T>
-__device__ __forceinline__ void group_entries(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g,
-                                              const T *__restrict__ coef, const T *__restrict__ x, T (&a)[G][6],
-                                              T (&xv)[G][6]) {
-    const int32_t n = L.n;
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int k = 2 - j;
-            if constexpr (kIn) {
-                a[u][j] = g.at(coef, u, k * n - L.d[k]);
-                xv[u][j] = g.at(x, u, -L.d[k]);
-            } else {
-                const int32_t c = g.row(u), col = c >= L.d[k] ? c - L.d[k] : n - 1;
-                a[u][j] = coef[k * n + col];
-                xv[u][j] = x[col];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            a[u][3 + k] = g.at(coef, u, k * n);
-            if constexpr (kIn) {
-                xv[u][3 + k] = g.at(x, u, L.d[k]);
-            } else {
-                const int32_t c = g.row(u);
-                xv[u][3 + k] = x[c < n - L.d[k] ? c + L.d[k] : c];
-            }
-        }
-    }
-}
-
 // y = acc + sum of the rows' entries
 template <int BS, int G, bool kIn, class T>
 __device__ __forceinline__ void group_dot(const BandLayout<3> &L, const RowGroup<BS, G, kIn> &g,
                                           const T *__restrict__ coef, const T *__restrict__ x, const T (&acc)[G],
                                           T (&y)[G]) {
     T a[G][6], xv[G][6];
-    group_entries(L, g, coef, x, a, xv);
+    group_entries(L, g, coef, MemVec<T>{x}, a, xv);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
         y[u] = acc[u];
@@ -172,7 +105,7 @@ __device__ __forceinline__ void group_assemble(const BandLayout<3> &L, const Row
                                                const double *__restrict__ x, double *__restrict__ coef,
                                                double (&lap)[G], double (&a)[G][6], double (&xv)[G][6]) {
     double dl[G][6];
-    group_entries(L, g, L.mag_sf, x, a, xv);
+    group_entries(L, g, L.mag_sf, MemVec<double>{x}, a, xv);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
 #pragma unroll

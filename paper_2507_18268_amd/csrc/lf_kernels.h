@@ -77,6 +77,16 @@ __device__ __forceinline__ int32_t walk_share(bool backward) {
     return backward && b < g8 ? (g8 - 8 - (b & ~7)) | (b & 7) : b;
 }
 
+// The share of workgroup blockIdx.x when each of the eight dies takes one
+// contiguous run of shares (workgroups go round the dies): a neighbour's value
+// is then mostly in the die's own L2.  Pays while the mesh is small enough to
+// sit in the caches; larger ones stream better in plain order.
+__device__ __forceinline__ int32_t die_share() {
+    const int32_t b = static_cast<int32_t>(blockIdx.x), nb = static_cast<int32_t>(gridDim.x);
+    const int32_t q = nb / kNumXcd, r = nb % kNumXcd, x = b % kNumXcd;
+    return x * q + (x < r ? x : r) + b / kNumXcd;
+}
+
 // first stage: the workgroup's partial sums go to part[slot * G + blockIdx.x]
 // (BS: threads of the workgroup; _at: the workgroup's index blk within its
 // problem's launch, for launches that serve several problems)
@@ -101,10 +111,11 @@ __device__ __forceinline__ void write_partials(double *__restrict__ part, int32_
 // a group (kU per slot, every slot) are issued together, so the serial chain
 // waits once per group: one or two groups at the sizes used here.
 // (BS: the threads of the workgroup that sums; the result is in every thread)
-template <int NQ, int BS = kFinBlock>
+// (U: loads of a group, 0: 32 over the slots' number)
+template <int NQ, int BS = kFinBlock, int U = 0>
 __device__ __forceinline__ void reduce_partials(const double *__restrict__ part, int32_t stride, int32_t G,
                                                 const int (&slot)[NQ], double (&out)[NQ]) {
-    constexpr int kU = NQ == 1 ? 32 : (NQ == 2 ? 16 : 8);
+    constexpr int kU = U > 0 ? U : NQ == 1 ? 32 : (NQ == 2 ? 16 : 8);
     double s[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) s[q] = 0.0;
@@ -156,10 +167,11 @@ struct MeshRows {
     const uint8_t *__restrict__ rlen;
 };
 
-// acc + sum_j a_j x[col_j] over the row's entries in order
-template <int W, class T, class A>
+// acc + sum_j a_j x[col_j] over the row's entries in order (X: a pointer, or a
+// vector formed where it is read)
+template <int W, class T, class X, class A>
 __device__ __forceinline__ A row_dot_w(int32_t base, int32_t len, const int32_t *__restrict__ scol,
-                                       const T *__restrict__ coef, const T *__restrict__ x, A acc) {
+                                       const T *__restrict__ coef, const X &x, A acc) {
     int32_t col[W];
     T a[W], xv[W];
     // the row's column indices and coefficients are read once per product:
@@ -177,9 +189,8 @@ __device__ __forceinline__ A row_dot_w(int32_t base, int32_t len, const int32_t 
     return acc;
 }
 
-template <class T, class A>
-__device__ __forceinline__ A row_dot(const MeshRows &mr, int32_t c, const T *__restrict__ coef,
-                                     const T *__restrict__ x, A acc) {
+template <class T, class X, class A>
+__device__ __forceinline__ A row_dot(const MeshRows &mr, int32_t c, const T *__restrict__ coef, const X &x, A acc) {
     const int32_t s = c >> 6;
     const int32_t o0 = mr.soff[s];
     const int32_t base = o0 + (c & (kSlice - 1));
@@ -409,6 +420,131 @@ __device__ __forceinline__ A layout_dot(const BandLayout<K> &L, int32_t c, const
 #pragma unroll
     for (int j = 0; j < 2 * K; ++j) acc += a[j] * xv[j];
     return acc;
+}
+
+// Rows of a workgroup of BS threads: thread t takes rows t, t + BS, ... of its
+// share in groups of G, whose loads are all issued before the first is used.
+// In an inner group (kIn) every row and every neighbour exists, so that a row's
+// arrays are one uniform base each and the thread's index, with no clamp and no
+// mask; the others (at the first and last rows of a mesh) read a clamped row
+// and mask it.
+template <int BS, int G, bool kIn>
+struct RowGroup {
+    uint32_t c0;         // the thread's first row of the group
+    int32_t last;        // n - 1
+    __device__ __forceinline__ bool ok(int u) const { return kIn || static_cast<int32_t>(c0) + u * BS <= last; }
+    __device__ __forceinline__ int32_t row(int u) const {
+        const int32_t c = static_cast<int32_t>(c0) + u * BS;
+        return kIn ? c : min(c, last);
+    }
+    // a[row u + off], off uniform
+    template <class T>
+    __device__ __forceinline__ T at(const T *__restrict__ a, int u, int32_t off = 0) const {
+        return kIn ? (a + off + u * BS)[c0] : a[row(u) + off];
+    }
+    template <class T>
+    __device__ __forceinline__ void set(T *__restrict__ a, int u, T v) const {
+        if (kIn) (a + u * BS)[c0] = v;
+        else if (ok(u)) a[row(u)] = v;
+    }
+};
+
+// a b + c, rounded once
+__device__ __forceinline__ float mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the vector a row product takes: an array, or the direction w + beta p formed
+// where it is read
+template <class T>
+struct MemVec {
+    const T *__restrict__ x;
+    template <class G>
+    __device__ __forceinline__ T at(const G &g, int u, int32_t off) const { return g.at(x, u, off); }
+    __device__ __forceinline__ T operator[](int32_t i) const { return x[i]; }
+};
+template <class T>
+struct DirVec {
+    const T *__restrict__ w, *__restrict__ p;
+    T beta;
+    template <class G>
+    __device__ __forceinline__ T at(const G &g, int u, int32_t off) const {
+        return g.at(w, u, off) + beta * g.at(p, u, off);
+    }
+    __device__ __forceinline__ T operator[](int32_t i) const { return w[i] + beta * p[i]; }
+};
+
+// the entries of the group's rows in layout_dot's order: coefficients and the
+// neighbours' x.  An entry outside the mesh takes band slot n - 1, which never
+// has a face and holds 0.
+template <int K, int BS, int G, bool kIn, class T, class X>
+__device__ __forceinline__ void group_entries(const BandLayout<K> &L, const RowGroup<BS, G, kIn> &g,
+                                              const T *__restrict__ coef, const X &x, T (&a)[G][2 * K],
+                                              T (&xv)[G][2 * K]) {
+    const int32_t n = L.n;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int k = K - 1 - j;
+            const T *__restrict__ ck = coef + static_cast<int64_t>(k) * n;
+            if constexpr (kIn) {
+                a[u][j] = g.at(ck, u, -L.d[k]);
+                xv[u][j] = x.at(g, u, -L.d[k]);
+            } else {
+                const int32_t c = g.row(u), col = c >= L.d[k] ? c - L.d[k] : n - 1;
+                a[u][j] = ck[col];
+                xv[u][j] = x[col];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            a[u][K + k] = g.at(coef + static_cast<int64_t>(k) * n, u);
+            if constexpr (kIn) {
+                xv[u][K + k] = x.at(g, u, L.d[k]);
+            } else {
+                const int32_t c = g.row(u);
+                xv[u][K + k] = x[c < n - L.d[k] ? c + L.d[k] : c];
+            }
+        }
+    }
+}
+
+// fn(rows) for workgroup blockIdx.x's R tiles of kCellBlock rows; halo: the rows
+// between a row and its farthest neighbour
+template <int R, class Fn>
+__device__ __forceinline__ void share_rows(const SolverParams &sp, int32_t halo, Fn &&fn) {
+    const int32_t n = sp.n;
+    const int32_t first = (sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x)) * R * kCellBlock;
+    const uint32_t c0 = static_cast<uint32_t>(first) + threadIdx.x;
+    if (first >= n) return;
+    if (first >= halo && first + R * kCellBlock <= n - halo)
+        fn(RowGroup<kCellBlock, R, true>{c0, n - 1});
+    else
+        fn(RowGroup<kCellBlock, R, false>{c0, n - 1});
+}
+
+template <int K>
+__device__ __forceinline__ int32_t row_halo(const BandLayout<K> &L) { return L.d[K - 1]; }
+__device__ __forceinline__ int32_t row_halo(const SellLayout &) { return 0; }    // its rows hold no outside entries
+
+// y_u = start(u) + the sum of row u's entries a_j x[col_j], in layout_dot's order
+template <int K, int G, bool kIn, class T, class X, class Start>
+__device__ __forceinline__ void row_sums(const BandLayout<K> &L, const RowGroup<kCellBlock, G, kIn> &g,
+                                         const T *__restrict__ coef, const X &x, Start &&start, T (&y)[G]) {
+    T a[G][2 * K], xv[G][2 * K];
+    group_entries(L, g, coef, x, a, xv);
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        y[u] = start(u);
+#pragma unroll
+        for (int j = 0; j < 2 * K; ++j) y[u] += a[u][j] * xv[u][j];
+    }
+}
+template <int G, bool kIn, class T, class X, class Start>
+__device__ __forceinline__ void row_sums(const SellLayout &L, const RowGroup<kCellBlock, G, kIn> &g,
+                                         const T *__restrict__ coef, const X &x, Start &&start, T (&y)[G]) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) y[u] = row_dot(L.mr, g.row(u), coef, x, start(u));
 }
 
 // ---------------------------------------------------------------------------

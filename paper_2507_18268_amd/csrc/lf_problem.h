@@ -87,10 +87,17 @@ inline bool box_walk_plan(int32_t n, int32_t K, const int32_t *d, int32_t W, Box
 }
 
 constexpr int kMaxGraphLog = 6;   // largest captured block: 64 iterations
-// FP64 solves with the diagonal preconditioner whose product and update write
-// at most this many partials per slot take the iteration's decisions inside
-// the update and direction kernels (every workgroup sums the partials)
-constexpr int32_t kFoldPartials = 512;
+// FP64 solves with the diagonal preconditioner and no walk run two launches per
+// iteration up to this many rows, one row per thread up to kFoldOneRow, else
+// kFoldRows in the product
+constexpr int32_t kFoldMaxRows = 2 << 20, kFoldOneRow = 1 << 19;
+constexpr int kFoldRows = 2;
+// up to this many rows its workgroups take contiguous shares per die: 100^3
+// 22.6 -> 20.2 us per product, 128^3 38.2 -> 38.5
+constexpr int32_t kFoldDieRows = 3 << 19;
+// the block walk's solves above this many partials per slot run on the
+// Jacobi-scaled matrix
+constexpr int32_t kScaledPartials = 512;
 
 struct SolverParams {
     double tol, rel_tol;
@@ -104,6 +111,8 @@ struct SolverParams {
     int32_t grid_mx_amul; // workgroups of the FP32 inner Amul launch (= its p.q partials)
     int32_t inner_restart;// mixed: 1 restarts the inner CG at every refinement pass
     int32_t grid_upd;     // workgroups of the FP64 update launch (= its |r| and w.r partials)
+    int32_t by_die;       // two-launch form: workgroups take contiguous shares per die
+    int32_t grid_sum;     // two-launch form: workgroups of the commit (= its partials of x0's sum), else 0
     double inner_tol;     // mixed: relative reduction of each inner solve
 };
 
@@ -149,9 +158,9 @@ struct lf_problem {
     bool rb2 = false;                          // DIC's kernels on the two-colour layout: two pairs per lane
     bool sumx_valid = false;                   // the part array holds the partial sums of the current T
                                                // (written by the FP64 commit; any other write of T clears it)
-    bool fold = false;                         // small diagonal FP64 solves: the iteration's reductions folded
-                                               // into the update and direction kernels
-    bool scaled = false;                       // diagonal FP64 solves on the block walk (not folded): CG on
+    bool fold = false;                         // diagonal FP64 solves of up to kFoldMaxRows rows: two launches
+                                               // per iteration (directions alternate between p and p2)
+    bool scaled = false;                       // diagonal FP64 solves on the block walk: CG on
                                                // the Jacobi-scaled matrix; during a solve rD holds sqrt(diagB),
                                                // r, p, q the scaled vectors and w the scaled iterate
     double *coefS = nullptr;                   // [3N] its off-diagonal band coefficients

@@ -18,6 +18,10 @@ inline int32_t update_blocks(int32_t n) {
     return n > 0 ? (n + kTile - 1) / kTile : 1;
 }
 
+inline int32_t fold_blocks(int32_t n) {
+    constexpr int32_t kTile = kCellBlock * kFoldRows;
+    return (n + kTile - 1) / kTile;
+}
 enum FinMode : int { kFinMean = 0, kFinStart = 1, kFinAlpha = 2, kFinBeta = 3, kFinConv = 4, kFinBetaOnly = 5 };
 template <int Mode>
 void launch_fin(lf_problem *P, hipStream_t s);
