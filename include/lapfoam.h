@@ -484,8 +484,8 @@ lf_status lf_batch_stats(lf_batch *batch, lf_solve_stats *stats, double *elapsed
  * those of lf_step on the same problem, alone or with any other members.
  * Stats of a member report no times (assemble_ms = solve_ms = 0).  While a
  * member runs it must not be stepped, reset, read, set or destroyed (those
- * calls return LF_ESTATE).  The group workspace holds the members' descriptors
- * and their gathered solver states; the group's own launches go to `stream`. */
+ * calls return LF_ESTATE).  The group workspace holds the members' descriptors;
+ * the group's own launches go to `stream`. */
 typedef struct lf_group lf_group;
 size_t lf_group_workspace_bytes(int32_t max_members);   /* max_members <= 32 */
 /* iters_per_block: inner iterations launched between two looks at the

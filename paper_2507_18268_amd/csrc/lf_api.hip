@@ -230,6 +230,14 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
         P->sp.grid_sum = update_blocks(m->N);
         P->sp.by_die = m->N <= kFoldDieRows ? 1 : 0;
     }
+    // the precision form without a walk: two launches per inner iteration
+    if (opts.precision == LF_PREC_MIXED && !P->walk) {
+        P->sp.mx_rows = m->N <= kMxOneRow ? 1 : (m->N <= kMxFoldStartRows ? kMxRows : kMxManyRows);
+        const int32_t tile = kCellBlock * P->sp.mx_rows;
+        P->sp.grid_mx = P->sp.grid_mx_amul = m->N > 0 ? (m->N - 1) / tile + 1 : 1;
+        P->sp.mx_fold_start = m->N <= kMxFoldStartRows ? 1 : 0;
+        P->sp.grid_sum = m->N <= kMxFoldMeanRows ? P->sp.grid : 0;
+    }
     // larger diagonal FP64 solves on the block walk iterate on the Jacobi-scaled
     // matrix (its coefficients carved by carve_problem for every FP64 diagonal
     // problem of a three-band layout); not the small ones (512 partials per
@@ -242,6 +250,7 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
     P->ws_bytes = dry.bytes();
     Carver cv(ws);
     carve_problem(cv, m, opts, P);
+    if (P->sp.mx_rows > 0) P->p32b = P->rD32;      // the batched kernel's array, free in the multi-kernel form
     auto fail = [&](lf_status st) { lf_problem_destroy(P); return st; };
     std::vector<int32_t> pt(std::max<int32_t>(m->P, 1), 0);
     std::vector<double> pv(std::max<int32_t>(m->P, 1), 0.0);

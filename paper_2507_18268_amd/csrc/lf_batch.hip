@@ -733,6 +733,7 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         t.n_bfaces = m->B;
         if (t.nb == 3) lds_rows = std::max(lds_rows, lds_vectors(t.n) * t.n);
     }
+    for (int32_t i = 0; i < n; ++i) problems[i]->sumx_valid = false;     // the launch rewrites T
     hipStream_t s = b->stream;
     int32_t g = n_workgroups > 0 ? std::min(n_workgroups, n) : n;
     LF_HIP(hipMemcpyAsync(b->d_tasks, b->h_tasks, sizeof(BatchTask) * n, hipMemcpyHostToDevice, s));

@@ -31,6 +31,7 @@ struct GroupMember {
     lf_solve_stats *stats = nullptr;
     const double *T0 = nullptr;     // copied in by the next launch
     bool start = false;             // the next launch starts step `step`
+    bool sum = false;               // and takes the sums of its T (later steps have the last residual's)
     bool turn = false;              // the next launch turns to the next refinement pass
     int32_t snap_step = -1;         // the next launch copies T into this step's snapshot
     bool final = false;             // the run ends once final_launch has completed
@@ -71,7 +72,7 @@ struct lf_group {
     hipStream_t stream = nullptr;
     int32_t max_members = 0, iters = 2;
     lf::MemberDesc *d_tab = nullptr, *h_tab = nullptr;
-    lf::PcgState *d_states = nullptr, *h_states = nullptr;
+    lf::PcgState *h_states = nullptr;   // pinned: the gather writes it
     std::vector<lf::GroupMember> members;
     hipEvent_t ev_block = nullptr;
     bool in_flight = false;
@@ -87,15 +88,14 @@ namespace {
 constexpr size_t align256(size_t b) { return (b + 255) & ~static_cast<size_t>(255); }
 
 size_t group_bytes(int32_t max_members) {
-    return align256(sizeof(MemberDesc) * static_cast<size_t>(max_members)) +
-           align256(sizeof(PcgState) * static_cast<size_t>(max_members));
+    return align256(sizeof(MemberDesc) * static_cast<size_t>(max_members));
 }
 
 lf_status check_member(const lf_group *g, const lf_problem *P) {
     if (P->opts.precision != LF_PREC_MIXED) { set_error("a group runs LF_PREC_MIXED problems"); return LF_EINVAL; }
     if (P->opts.precond != LF_PC_DIAGONAL) { set_error("a group runs the diagonal preconditioner"); return LF_EINVAL; }
     if (P->nonorth) { set_error("a group runs orthogonal meshes (no corrector loop)"); return LF_EINVAL; }
-    if (P->walk || P->box || P->rb) {
+    if (P->walk || P->box || P->rb || P->sp.mx_rows <= 0) {
         set_error("a group runs the one-row-per-thread products (lf_problem_amul_walk 0)");
         return LF_EINVAL;
     }
@@ -110,15 +110,21 @@ lf_status check_member(const lf_group *g, const lf_problem *P) {
     return LF_OK;
 }
 
-// the members of a launch, each with `count(member)` workgroups
+// the members of a launch, each with `count(member)` shares; as many shares per
+// workgroup as leave about kGroupBlocks workgroups (four per CU)
+constexpr int64_t kGroupBlocks = 1024, kGroupMaxShares = 8;
+
 template <class Count>
 GroupLaunch launch_of(const lf_group *g, const std::vector<int32_t> &slots, Count &&count) {
     GroupLaunch gl{};
+    int64_t shares = 0;
+    for (const int32_t s : slots) shares += count(g->members[s]);
+    gl.per = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(kGroupMaxShares, shares / kGroupBlocks)));
     int64_t blocks = 0;
     for (const int32_t s : slots) {
         gl.slot[gl.n] = s;
         gl.begin[gl.n] = static_cast<int32_t>(blocks);
-        blocks += count(g->members[s]);
+        blocks += (count(g->members[s]) + gl.per - 1) / gl.per;
         ++gl.n;
     }
     gl.begin[gl.n] = static_cast<int32_t>(std::min<int64_t>(blocks, INT32_MAX));
@@ -175,6 +181,7 @@ lf_status consume(lf_group *g) {
     for (auto &m : g->members) {
         if (!m.P || !m.final || m.final_launch < 0 || m.final_launch > completed) continue;
         m.P->group = nullptr;
+        m.P->sumx_valid = !m.sum;       // false where no step has started
         g->done.push_back(m.P);
         m = GroupMember{};
     }
@@ -225,32 +232,40 @@ lf_status launch_next(lf_group *g) {
     if (in.n) hipLaunchKernelGGL(k_grp_copy, dim3(static_cast<unsigned>(in_blocks)), dim3(kBlock), 0, st, in);
     const auto cells = [](const GroupMember &m) { return static_cast<int64_t>(m.P->sp.grid); };
     const auto inner_blocks = [](const GroupMember &m) { return static_cast<int64_t>(m.P->sp.grid_mx); };
+    // those whose start of a pass the one-workgroup kernels decide
+    const auto big = [](const GroupMember &m) { return !m.P->sp.mx_fold_start; };
+    const auto select = [g](const std::vector<int32_t> &slots, auto &&which) {
+        std::vector<int32_t> v;
+        for (const int32_t s : slots)
+            if (which(g->members[s])) v.push_back(s);
+        return v;
+    };
     if (!starts.empty()) {
         const GroupLaunch gl = launch_of(g, starts, cells);
-        launch_group_setup(g->d_tab, gl, st);
+        launch_group_setup(g->d_tab, gl, launch_of(g, select(starts, [](const GroupMember &m) { return m.sum; }), cells),
+                           launch_of(g, select(starts, [](const GroupMember &m) { return m.P->sp.grid_sum == 0; }), cells),
+                           st);
         launch_group_scale(g->d_tab, gl, st);
-        launch_group_fin_start(g->d_tab, gl, st);
-        launch_group_pass_start(g->d_tab, gl, st);
+        launch_group_solve_start(g->d_tab, launch_of(g, starts, inner_blocks), launch_of(g, select(starts, big), cells),
+                                 st);
         for (const int32_t s : starts) {
             GroupMember &m = g->members[s];
             m.start = false;
+            m.sum = false;
             m.P->assembled = true;
             m.P->scaled32 = true;
         }
     }
     if (!turns.empty()) {
         const GroupLaunch gl = launch_of(g, turns, cells);
-        launch_group_pass_end(g->d_tab, gl, st);
-        launch_group_pass_start(g->d_tab, gl, st);
+        launch_group_turn(g->d_tab, gl, launch_of(g, turns, inner_blocks), launch_of(g, select(turns, big), cells), st);
         for (const int32_t s : turns) g->members[s].turn = false;
     }
     GroupLaunch gi{};
     if (!inner.empty()) {
         gi = launch_of(g, inner, inner_blocks);
         for (int32_t k = 0; k < g->iters; ++k) launch_group_iteration(g->d_tab, gi, st);
-        launch_group_gather(g->d_tab, gi, g->d_states, st);
-        LF_HIP(hipMemcpyAsync(g->h_states, g->d_states, sizeof(PcgState) * static_cast<size_t>(g->max_members),
-                              hipMemcpyDeviceToHost, st));
+        launch_group_gather(g->d_tab, gi, g->h_states, st);
     }
     LF_HIP(hipGetLastError());
     LF_HIP(hipEventRecord(g->ev_block, st));
@@ -301,7 +316,6 @@ lf_status lf_group_create(int32_t max_members, int32_t iters_per_block, void *ws
     g->members.resize(static_cast<size_t>(max_members));
     char *base = static_cast<char *>(ws);
     g->d_tab = reinterpret_cast<MemberDesc *>(base);
-    g->d_states = reinterpret_cast<PcgState *>(base + align256(sizeof(MemberDesc) * max_members));
     hipError_t e = hipGetDevice(&g->device);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&g->h_tab), sizeof(MemberDesc) * max_members,
                                            hipHostMallocDefault);
@@ -354,6 +368,7 @@ lf_status lf_group_add(lf_group *g, lf_problem *P, int32_t n_steps, const double
     m.stats = stats;
     m.T0 = T0;
     m.start = true;
+    m.sum = T0 != nullptr || !P->sumx_valid;
     P->group = g;
     return LF_OK;
 }

@@ -285,17 +285,41 @@ struct MemberDesc {
     double *T, *coef, *diagB, *srcB, *r, *rD, *p;
     const float *coef32;
     float *coef32w, *sig32;
-    float *r32, *p32, *d32, *q32;
+    float *r32, *p32, *p32b, *d32, *q32;
     double *part;
     PcgState *st;
 };
 
+// a member's descriptor with its pointers known to be global ones
+__device__ __forceinline__ MemberDesc global_member(const MemberDesc &t) {
+    MemberDesc m = t;
+    m.mr = MeshRows{as_global(t.mr.soff), as_global(t.mr.scol), as_global(t.mr.sface), as_global(t.mr.rlen)};
+    m.mag_sf = as_global(t.mag_sf); m.delta = as_global(t.delta);
+    m.emag_sf = as_global(t.emag_sf); m.edelta = as_global(t.edelta);
+    m.bface_start = as_global(t.bface_start); m.bface_list = as_global(t.bface_list);
+    m.bface_patch = as_global(t.bface_patch);
+    m.bmag_sf = as_global(t.bmag_sf); m.bdelta = as_global(t.bdelta); m.V = as_global(t.V);
+    m.patch_type = as_global(t.patch_type); m.patch_value = as_global(t.patch_value);
+    m.iperm = as_global(t.iperm);
+    m.T = as_global(t.T); m.coef = as_global(t.coef); m.diagB = as_global(t.diagB); m.srcB = as_global(t.srcB);
+    m.r = as_global(t.r); m.rD = as_global(t.rD); m.p = as_global(t.p);
+    m.coef32 = as_global(t.coef32); m.coef32w = as_global(t.coef32w); m.sig32 = as_global(t.sig32);
+    m.r32 = as_global(t.r32); m.p32 = as_global(t.p32); m.p32b = as_global(t.p32b);
+    m.d32 = as_global(t.d32); m.q32 = as_global(t.q32);
+    m.part = as_global(t.part); m.st = as_global(t.st);
+    return m;
+}
+
 constexpr int kGroupMax = 32;   // problems of one group
 
 // the members of one group launch: table slots and their first workgroups
-// (begin[n] = the launch's workgroups)
+// (begin[n] = the launch's workgroups).  A workgroup takes `per` consecutive
+// shares of its member, each with the partial sums it has in the member's own
+// launch: reading the descriptor and summing the partials costs a workgroup
+// several microseconds, which one share of 512 or 1024 rows does not cover.
 struct GroupLaunch {
     int32_t n;
+    int32_t per;
     int32_t slot[kGroupMax];
     int32_t begin[kGroupMax + 1];
 };
@@ -312,12 +336,28 @@ __device__ __forceinline__ void with_member_layout(const MemberDesc &m, Fn &&fn)
     }
 }
 
-// the member of a group launch that workgroup b belongs to (members' first
-// workgroups in gl.begin)
+// the member of a group launch that workgroup b belongs to: each lane looks at
+// one member's first workgroup (kGroupMax is at most a wavefront)
 __device__ __forceinline__ int32_t group_member(const GroupLaunch &gl, int32_t b) {
-    int32_t i = 0;
-    while (i + 1 < gl.n && b >= gl.begin[i + 1]) ++i;
-    return i;
+    static_assert(kGroupMax <= 64, "a wavefront's lanes look at the members");
+    const int32_t l = static_cast<int32_t>(threadIdx.x) & 63;
+    const bool at_or_past = l > 0 && l < gl.n && b >= gl.begin[l < kGroupMax ? l : 0];
+    return __popcll(__ballot(at_or_past));
+}
+
+// a group launch's workgroup: its member and shares [share, end) of `total`
+struct GroupShare {
+    int32_t member, share, end;
+    bool lead;
+};
+__device__ __forceinline__ GroupShare group_share(const GroupLaunch &gl, int32_t b) {
+    GroupShare s;
+    s.member = group_member(gl, b);
+    const int32_t blk = b - gl.begin[s.member];
+    s.share = blk * gl.per;
+    s.end = s.share + gl.per;
+    s.lead = blk == 0;
+    return s;
 }
 
 // Row c's entries: coefficient slot, column and whether the entry may hold a
@@ -473,6 +513,19 @@ struct DirVec {
     __device__ __forceinline__ T operator[](int32_t i) const { return w[i] + beta * p[i]; }
 };
 
+// gamma w + beta p (the first direction of a pass that continues the last one's
+// CG; gamma = 1 otherwise)
+template <class T>
+struct Dir2Vec {
+    const T *__restrict__ w, *__restrict__ p;
+    T gamma, beta;
+    template <class G>
+    __device__ __forceinline__ T at(const G &g, int u, int32_t off) const {
+        return gamma * g.at(w, u, off) + beta * g.at(p, u, off);
+    }
+    __device__ __forceinline__ T operator[](int32_t i) const { return gamma * w[i] + beta * p[i]; }
+};
+
 // the entries of the group's rows in layout_dot's order: coefficients and the
 // neighbours' x.  An entry outside the mesh takes band slot n - 1, which never
 // has a face and holds 0.
@@ -509,18 +562,22 @@ __device__ __forceinline__ void group_entries(const BandLayout<K> &L, const RowG
     }
 }
 
-// fn(rows) for workgroup blockIdx.x's R tiles of kCellBlock rows; halo: the rows
-// between a row and its farthest neighbour
+// fn(rows) for the R tiles of kCellBlock rows from row `first` on; halo: the
+// rows between a row and its farthest neighbour
 template <int R, class Fn>
-__device__ __forceinline__ void share_rows(const SolverParams &sp, int32_t halo, Fn &&fn) {
-    const int32_t n = sp.n;
-    const int32_t first = (sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x)) * R * kCellBlock;
+__device__ __forceinline__ void rows_from(int32_t first, int32_t n, int32_t halo, Fn &&fn) {
     const uint32_t c0 = static_cast<uint32_t>(first) + threadIdx.x;
     if (first >= n) return;
     if (first >= halo && first + R * kCellBlock <= n - halo)
         fn(RowGroup<kCellBlock, R, true>{c0, n - 1});
     else
         fn(RowGroup<kCellBlock, R, false>{c0, n - 1});
+}
+
+// workgroup blockIdx.x's tiles of the two-launch form
+template <int R, class Fn>
+__device__ __forceinline__ void share_rows(const SolverParams &sp, int32_t halo, Fn &&fn) {
+    rows_from<R>((sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x)) * R * kCellBlock, sp.n, halo, fn);
 }
 
 template <int K>

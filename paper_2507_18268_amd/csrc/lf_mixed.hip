@@ -57,7 +57,7 @@ void carve_mixed(Carver &cv, const lf_mesh *m, bool banded, lf_problem *P) {
     if (P) {
         P->bic = bic; P->bbc = bbc;
         P->coef32 = coef32; P->diag32 = v32[0]; P->rD32 = v32[1]; P->r32 = v32[2];
-        P->p32 = v32[3]; P->q32 = v32[4]; P->d32 = v32[5]; P->sig32 = v32[6];
+        P->p32 = P->p32b = v32[3]; P->q32 = v32[4]; P->d32 = v32[5]; P->sig32 = v32[6];
     }
 }
 
@@ -158,38 +158,10 @@ k_mx_direction(SolverParams sp, const float *__restrict__ r32, float *__restrict
     mx_direction(walk_share((st->inner_iter & 1) != 0), sp, r32, p32, d32, st);
 }
 
-// q = As p in FP32 (unit diagonal: p_c first, then the row's entries in
-// order); FP64 partial sums of p.q
-template <class Lay>
-__device__ __forceinline__ void mx_amul_dot(int32_t blk, const SolverParams &sp, const Lay &L,
-                                            const float *__restrict__ coef32, const float *__restrict__ p32,
-                                            float *__restrict__ q32, double *__restrict__ part,
-                                            const PcgState *__restrict__ st) {
-    if (inner_off(st)) return;
-    double acc[1] = {0.0};
-#pragma unroll
-    for (int j = 0; j < kMxRows; ++j) {
-        const int32_t c = cell_row_at<kMxRows>(blk, j);
-        if (c >= sp.n) continue;
-        const float pc = p32[c];
-        const float qc = layout_dot(L, c, coef32, p32, pc);
-        __builtin_nontemporal_store(qc, &q32[c]);
-        acc[0] += static_cast<double>(qc) * static_cast<double>(pc);
-    }
-    const int slots[1] = {kPartPq};
-    write_partials_at<1>(part, sp.grid_mx, blk, slots, acc);
-}
-
-template <class Lay>
-__global__ void __launch_bounds__(kCellBlock)
-k_mx_amul_dot(SolverParams sp, Lay L, const float *__restrict__ coef32, const float *__restrict__ p32,
-              float *__restrict__ q32, double *__restrict__ part, const PcgState *__restrict__ st) {
-    mx_amul_dot(static_cast<int32_t>(blockIdx.x), sp, L, coef32, p32, q32, part, st);
-}
-
-// the same product by the row walk (band layouts with two or more bands):
+// q = As p in FP32 (unit diagonal: p_c first, then the row's entries in order)
+// by the row walk (band layouts with two or more bands), FP64 partial sums of p.q:
 // sp.grid_mx_amul workgroups, whose partials fill the start of the p.q slot
-// (slots sp.grid_mx apart)
+// (slots sp.grid apart)
 template <int K>
 __global__ void __launch_bounds__(kCellBlock)
 k_mx_amul_dot_walk(SolverParams sp, BandLayout<K> L, const float *__restrict__ coef32,
@@ -198,7 +170,7 @@ k_mx_amul_dot_walk(SolverParams sp, BandLayout<K> L, const float *__restrict__ c
     if (inner_off(st)) return;
     double acc[1] = {band_walk<K, true, true, float>(L, nullptr, coef32, p32, q32)};
     const int slots[1] = {kPartPq};
-    write_partials<1>(part, sp.grid_mx, slots, acc);
+    write_partials<1>(part, sp.grid, slots, acc);
 }
 
 // the same product by the block walk of a box, four rows per lane (bw.blocks
@@ -217,7 +189,7 @@ k_mx_amul_dot_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const float *__r
         for (int w = 0; w < 4; ++w) acc[0] += static_cast<double>(qc.v[w]) * static_cast<double>(pc.v[w]);
     });
     const int slots[1] = {kPartPq};
-    write_partials_at<1, kBwBlock>(part, sp.grid_mx, blk, slots, acc);
+    write_partials_at<1, kBwBlock>(part, sp.grid, blk, slots, acc);
 }
 
 // rs -= alpha q (FP32); FP64 partials of the L1 norm s|rs| and of rs.rs
@@ -237,7 +209,7 @@ __device__ __forceinline__ void mx_update(int32_t blk, const SolverParams &sp, c
         acc[1] += static_cast<double>(rc) * static_cast<double>(rc);
     }
     const int slots[2] = {kPartSumR, kPartWr};
-    write_partials_at<2>(part, sp.grid_mx, blk, slots, acc);
+    write_partials_at<2>(part, sp.grid, blk, slots, acc);
 }
 
 __global__ void __launch_bounds__(kCellBlock)
@@ -246,13 +218,21 @@ k_mx_update(SolverParams sp, const float *__restrict__ q32, const float *__restr
     mx_update(walk_share((st->inner_iter & 1) != 0), sp, q32, sig32, r32, part, st);
 }
 
+// the direction of the solve's inner iteration n_iter - 1, the last one: two
+// launches per iteration keep iteration i's in buffer i & 1 (counted over the
+// passes), the walks' kernels all in p32 (p32b = p32)
+__device__ __forceinline__ const float *last_dir(int32_t n_iter, const float *p32, const float *p32b) {
+    return n_iter & 1 ? p32 : p32b;
+}
+
 // T += d = (y + alpha p) / s in FP64, alpha p being the last inner update
 // when it is still pending
 __device__ __forceinline__ void mx_correct(int32_t blk, const SolverParams &sp, double *__restrict__ T,
-                                           const float *__restrict__ d32, const float *__restrict__ p32,
-                                           const float *__restrict__ sig32, const PcgState *__restrict__ st) {
+                                           const float *__restrict__ d32, const float *__restrict__ p32a,
+                                           const float *__restrict__ p32b, const float *__restrict__ sig32, const PcgState *__restrict__ st) {
     if (st->done) return;
     const bool pend = st->inner_pend != 0;
+    const float *__restrict__ p32 = last_dir(st->n_iter, p32a, p32b);
     const float alpha = static_cast<float>(st->alpha);
     const int32_t c = blk * kCellBlock + static_cast<int32_t>(threadIdx.x);
     if (c < sp.n) {
@@ -264,8 +244,8 @@ __device__ __forceinline__ void mx_correct(int32_t blk, const SolverParams &sp, 
 
 __global__ void __launch_bounds__(kCellBlock)
 k_mx_correct(SolverParams sp, double *__restrict__ T, const float *__restrict__ d32, const float *__restrict__ p32,
-             const float *__restrict__ sig32, const PcgState *__restrict__ st) {
-    mx_correct(static_cast<int32_t>(blockIdx.x), sp, T, d32, p32, sig32, st);
+             const float *__restrict__ p32b, const float *__restrict__ sig32, const PcgState *__restrict__ st) {
+    mx_correct(static_cast<int32_t>(blockIdx.x), sp, T, d32, p32, p32b, sig32, st);
 }
 
 // one row of a pass end: from ax = (A T)_c, the FP64 residual r and the start
@@ -291,28 +271,39 @@ template <class Lay>
 __device__ __forceinline__ void mx_residual(int32_t blk, const SolverParams &sp, const Lay &L,
                                             const double *__restrict__ diagB, const double *__restrict__ coef,
                                             const double *__restrict__ srcB, const double *__restrict__ T,
-                                            const float *__restrict__ p32, float *__restrict__ r32,
-                                            float *__restrict__ d32, double *__restrict__ part,
-                                            const PcgState *__restrict__ st) {
+                                            const float *__restrict__ p32, const float *__restrict__ p32b,
+                                            float *__restrict__ r32, float *__restrict__ d32,
+                                            double *__restrict__ part, PcgState *__restrict__ st) {
     if (st->done) return;
     const bool keep = st->inner_iter > 0;
+    if (blk == 0 && threadIdx.x == 0) {
+        // for the launch that turns to the next pass, whose workgroup 0 overwrites them
+        st->n_outer_prev = st->n_outer;
+        st->inner_iter_prev = st->inner_iter;
+        st->wArA_prev = st->wArA;
+    }
+    const float *__restrict__ pl = last_dir(st->n_iter, p32, p32b);
     const int32_t c = blk * kCellBlock + static_cast<int32_t>(threadIdx.x);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double a5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (c < sp.n) {
-        const double db = diagB[c];
-        pass_end_row(c, layout_dot(L, c, coef, T, db * T[c]), db, keep, srcB, p32, r32, d32, acc);
+        const double db = diagB[c], tc = T[c];
+        pass_end_row(c, layout_dot(L, c, coef, T, db * tc), db, keep, srcB, pl, r32, d32, acc);
+        a5[4] = tc;                 // the sum of x0 for the next solve's mean
     }
-    const int slots[4] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32};
-    write_partials_at<4>(part, sp.grid, blk, slots, acc);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a5[j] = acc[j];
+    const int slots[5] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32, kPartSumX};
+    write_partials_at<5>(part, sp.grid, blk, slots, a5);
 }
 
 template <class Lay>
 __global__ void __launch_bounds__(kCellBlock)
 k_mx_residual(SolverParams sp, Lay L, const double *__restrict__ diagB, const double *__restrict__ coef,
               const double *__restrict__ srcB, const double *__restrict__ T, const float *__restrict__ p32,
-              float *__restrict__ r32, float *__restrict__ d32, double *__restrict__ part,
-              const PcgState *__restrict__ st) {
-    mx_residual(static_cast<int32_t>(blockIdx.x), sp, L, diagB, coef, srcB, T, p32, r32, d32, part, st);
+              const float *__restrict__ p32b, float *__restrict__ r32, float *__restrict__ d32,
+              double *__restrict__ part, PcgState *__restrict__ st) {
+    mx_residual(static_cast<int32_t>(blockIdx.x), sp, L, diagB, coef, srcB, T, p32, p32b, r32, d32, part, st);
 }
 
 // the same residual by the row walk (sp.grid_amul workgroups)
@@ -367,14 +358,73 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
     write_partials_at<4, kBwBlock>(part, sp.grid, blk, slots, acc);
 }
 
+// The start of an inner solve from the sums v of s|rs|, rs.rs and rs.p.
+// A later pass continues the CG of the one before (which iterated): the true
+// residual replaces the recurred one, and the last direction p is kept, made
+// orthogonal to it (rs.p = 0, which CG's alpha = rs.rs / p.Ap assumes):
+// p = gamma rs + beta p with beta = rs.rs / (rs.rs before the replacement) and
+// gamma = 1 - beta rs.p / rs.rs
+struct InnerStart {
+    double target, beta, gamma;
+    bool cont, off, bad;      // off: nothing to iterate; bad: non-finite
+};
+__device__ __forceinline__ void inner_start(const SolverParams &sp, double nf, const double (&v)[3], int32_t n_outer,
+                                            int32_t inner_iter, double wArA, InnerStart &is) {
+    is.target = fmax(sp.inner_tol * v[0], 0.5 * kTighten * sp.tol * nf);
+    is.cont = !sp.inner_restart && n_outer > 0 && inner_iter > 0 && wArA > 0.0 && v[1] > 0.0 && isfinite(v[1]) &&
+              isfinite(v[2]);
+    is.beta = 0.0;
+    is.gamma = 1.0;
+    if (is.cont) {
+        is.beta = v[1] / wArA;
+        is.gamma = 1.0 - is.beta * (v[2] / v[1]);
+    }
+    is.off = v[0] <= is.target || !(v[1] > 0.0);
+    is.bad = !isfinite(v[0]) || !isfinite(v[1]);
+}
+__device__ __forceinline__ void record_inner_start(const InnerStart &is, const double (&v)[3],
+                                                   PcgState *__restrict__ st) {
+    st->inner_cont = is.cont ? 1 : 0;
+    if (is.cont) {
+        st->beta = is.beta;
+        st->gamma = is.gamma;
+    }
+    st->inner_target = is.target;
+    st->inner_iter = 0;
+    st->inner_pend = 0;
+    st->alpha = 0.0;
+    st->wArA = v[1];
+    st->inner_done = is.off ? 1 : 0;
+    if (is.bad) {
+        st->nonfinite = 1;
+        st->done = 1;
+    }
+}
+
+// The outer check after pass n_outer (counted from 1): true if the solve goes on
+__device__ __forceinline__ bool outer_check(const SolverParams &sp, double res, double res0, int32_t n_outer,
+                                            int32_t n_iter, PcgState *__restrict__ st, bool record) {
+    const bool conv = check_conv(res, res0, sp.tol, sp.rel_tol);
+    const bool tight = check_conv(res, res0, kTighten * sp.tol, kTighten * sp.rel_tol);
+    const bool bad = !isfinite(res);
+    const bool stop = bad || tight || n_outer >= sp.max_outer || n_iter >= sp.max_iter;
+    if (record) {
+        st->res = res;
+        st->n_outer = n_outer;
+        st->converged = conv ? 1 : 0;
+        if (bad) st->nonfinite = 1;
+        if (stop) st->done = 1;
+    }
+    return !stop;
+}
+
 // one-workgroup decisions of the refinement
 enum MxFin : int { kMxInnerStart = 0, kMxAlpha = 1, kMxBeta = 2, kMxOuter = 3 };
 
 template <int Mode>
 __device__ __forceinline__ void mx_finalize(const SolverParams &sp, const double *__restrict__ part,
                                             PcgState *__restrict__ st) {
-    // partials per slot: the FP32 inner kernels use their own grid
-    const int32_t G = (Mode == kMxAlpha || Mode == kMxBeta) ? sp.grid_mx : sp.grid;
+    const int32_t G = sp.grid;        // the slots' stride
     if (Mode == kMxInnerStart) {
         if (st->done) return;
         // the first pass starts from the assembly's partials (sp.grid of them),
@@ -382,33 +432,9 @@ __device__ __forceinline__ void mx_finalize(const SolverParams &sp, const double
         double v[3];
         const int slots[3] = {kPartSumR32, kPartWr32, kPartRp32};
         reduce_partials<3>(part, G, st->n_outer == 0 ? sp.grid : sp.grid_amul, slots, v);
-        if (threadIdx.x == 0) {
-            const double target = fmax(sp.inner_tol * v[0], 0.5 * kTighten * sp.tol * st->nf);
-            // a later pass continues the CG of the one before (which iterated):
-            // the true residual replaces the recurred one, and the last
-            // direction p is kept, made orthogonal to it (rs.p = 0, which CG's
-            // alpha = rs.rs / p.Ap assumes): p = gamma rs + beta p with
-            // beta = rs.rs / (rs.rs before the replacement) and
-            // gamma = 1 - beta rs.p / rs.rs
-            const bool cont = !sp.inner_restart && st->n_outer > 0 && st->inner_iter > 0 && st->wArA > 0.0 &&
-                              v[1] > 0.0 && isfinite(v[1]) && isfinite(v[2]);
-            st->inner_cont = cont ? 1 : 0;
-            if (cont) {
-                const double beta = v[1] / st->wArA;
-                st->beta = beta;
-                st->gamma = 1.0 - beta * (v[2] / v[1]);
-            }
-            st->inner_target = target;
-            st->inner_iter = 0;
-            st->inner_pend = 0;
-            st->alpha = 0.0;
-            st->wArA = v[1];
-            st->inner_done = (v[0] <= target || !(v[1] > 0.0)) ? 1 : 0;
-            if (!isfinite(v[0]) || !isfinite(v[1])) {
-                st->nonfinite = 1;
-                st->done = 1;
-            }
-        }
+        InnerStart is;
+        inner_start(sp, st->nf, v, st->n_outer, st->inner_iter, st->wArA, is);
+        if (threadIdx.x == 0) record_inner_start(is, v, st);
     } else if (Mode == kMxAlpha) {
         if (inner_off(st)) return;
         // the Amul launch wrote sp.grid_mx_amul partials
@@ -431,7 +457,7 @@ __device__ __forceinline__ void mx_finalize(const SolverParams &sp, const double
         if (inner_off(st)) return;
         double v[2];
         const int slots[2] = {kPartSumR, kPartWr};
-        reduce_partials<2>(part, G, slots, v);
+        reduce_partials<2>(part, G, sp.grid_mx, slots, v);
         if (threadIdx.x == 0) {
             st->inner_pend = 1;              // y += alpha p of this iteration is pending
             st->inner_iter += 1;
@@ -451,20 +477,7 @@ __device__ __forceinline__ void mx_finalize(const SolverParams &sp, const double
         double v[1];
         const int slots[1] = {kPartSumR};
         reduce_partials<1>(part, G, sp.grid_amul, slots, v);     // the residual launch's partials
-        if (threadIdx.x == 0) {
-            const double res = v[0] / st->nf;
-            st->res = res;
-            st->n_outer += 1;
-            const bool conv = check_conv(res, st->res0, sp.tol, sp.rel_tol);
-            const bool tight = check_conv(res, st->res0, kTighten * sp.tol, kTighten * sp.rel_tol);
-            st->converged = conv ? 1 : 0;
-            if (!isfinite(res)) {
-                st->nonfinite = 1;
-                st->done = 1;
-            } else if (tight || st->n_outer >= sp.max_outer || st->n_iter >= sp.max_iter) {
-                st->done = 1;
-            }
-        }
+        if (threadIdx.x == 0) (void)outer_check(sp, v[0] / st->nf, st->res0, st->n_outer + 1, st->n_iter, st, true);
     }
 }
 
@@ -475,6 +488,261 @@ __global__ void __launch_bounds__(kFinBlock) k_mx_finalize(SolverParams sp, cons
 }
 
 // ---------------------------------------------------------------------------
+// Meshes without a walk: two launches per inner iteration (the launches bound
+// it there: five of 4 to 6 us each before).  As in the FP64 solve's two-launch
+// form the product forms the new direction where it reads it, and the sums'
+// second stage and the decisions are taken by every workgroup of the next
+// kernel.  Inner iteration i of the step (counted over its passes) keeps its
+// direction in buffer i & 1.  State values that workgroup 0 overwrites are read
+// by the others from copies the launch before made.
+// ---------------------------------------------------------------------------
+enum MxDir : int { kMxNext = 0, kMxSolve = 1, kMxPass = 2 };
+
+// inner_off as one value for the whole workgroup
+__device__ __forceinline__ bool group_inner_off(const PcgState *__restrict__ st) {
+    __shared__ int32_t s_off;
+    if (threadIdx.x == 0) s_off = inner_off(st) ? 1 : 0;
+    __syncthreads();
+    return s_off != 0;
+}
+
+struct MxStep {
+    float alpha, beta, gamma;
+    int32_t i;          // the iteration
+    bool cont;          // its direction takes the last one in
+};
+
+// The decisions ahead of the next direction, false where there is none: after an
+// iteration's update (kMxNext), at the start of a solve (kMxSolve: normalisation
+// factor, initial residual, start of the first pass) and at a pass's end
+// (kMxPass: outer check, start of the next pass).
+template <int kMode>
+__device__ __forceinline__ bool mx_take(const SolverParams &sp, bool lead, const double *__restrict__ part,
+                                        PcgState *__restrict__ st, MxStep &s) {
+    s.alpha = s.beta = 0.0f;
+    s.gamma = 1.0f;
+    s.i = 0;
+    s.cont = false;
+    if constexpr (kMode == kMxNext) {
+        if (group_inner_off(st)) return false;
+        double v[2];
+        const int ps[2] = {kPartSumR, kPartWr};
+        reduce_partials<2, kCellBlock, 4>(part, sp.grid, sp.grid_mx, ps, v);
+        s.i = st->n_iter_prev + 1;
+        const bool bad = !isfinite(v[0]) || !isfinite(v[1]);
+        const bool off = bad || v[0] <= st->inner_target || s.i >= sp.max_iter || !(v[1] > 0.0);
+        const double beta = v[1] / st->wArA_prev;
+        s.alpha = static_cast<float>(st->alpha);
+        s.beta = static_cast<float>(beta);
+        s.cont = true;
+        if (lead) {
+            st->inner_iter = st->inner_iter + 1;
+            st->n_iter = s.i;
+            st->inner_pend = off ? 1 : 0;       // y += alpha p: applied by the direction, or pending
+            if (bad) {
+                st->nonfinite = 1;
+                st->done = 1;
+            } else if (off) {
+                st->inner_done = 1;
+            } else {
+                st->beta = beta;
+                st->wArA = v[1];
+            }
+        }
+        return !off;
+    } else if (!sp.mx_fold_start) {
+        // the one-workgroup kernels have taken the decisions
+        if (group_inner_off(st)) return false;
+        s.i = st->n_iter;
+        s.cont = st->inner_cont != 0;
+        if (s.cont) {
+            s.beta = static_cast<float>(st->beta);
+            s.gamma = static_cast<float>(st->gamma);
+        }
+        return true;
+    } else {
+        double nf, v[3];
+        int32_t n_outer = 0, inner_iter = 0;
+        double wArA = 0.0;
+        if constexpr (kMode == kMxSolve) {
+            double a[4];
+            const int ps[4] = {kPartNf, kPartSumR, kPartSumR32, kPartWr32};
+            reduce_partials<4, kCellBlock, 4>(part, sp.grid, sp.grid, ps, a);
+            nf = a[0] + 1e-20;
+            const double res0 = a[1] / nf;
+            const bool conv = check_conv(res0, res0, sp.tol, sp.rel_tol);
+            const bool bad = !isfinite(res0);
+            const bool stop = bad || !(sp.min_iter > 0 || !conv);
+            if (lead) {
+                st->nf = nf;
+                st->res0 = res0;
+                st->res = res0;
+                st->converged = conv ? 1 : 0;
+                st->wArA = 0.0;
+                if (bad) st->nonfinite = 1;
+                if (stop) st->done = 1;
+            }
+            if (stop) return false;
+            v[0] = a[2];
+            v[1] = a[3];
+            v[2] = 0.0;
+        } else {
+            __shared__ int32_t s_done;
+            if (threadIdx.x == 0) s_done = st->done;
+            __syncthreads();
+            if (s_done) return false;
+            double a[4];
+            const int ps[4] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32};
+            reduce_partials<4, kCellBlock, 4>(part, sp.grid, sp.grid, ps, a);
+            nf = st->nf;
+            n_outer = st->n_outer_prev + 1;
+            s.i = st->n_iter;
+            if (!outer_check(sp, a[0] / nf, st->res0, n_outer, s.i, st, lead)) return false;
+            v[0] = a[1];
+            v[1] = a[2];
+            v[2] = a[3];
+            inner_iter = st->inner_iter_prev;
+            wArA = st->wArA_prev;
+        }
+        InnerStart is;
+        inner_start(sp, nf, v, n_outer, inner_iter, wArA, is);
+        if (lead) record_inner_start(is, v, st);
+        s.cont = is.cont;
+        s.beta = static_cast<float>(is.beta);
+        s.gamma = static_cast<float>(is.gamma);
+        return !is.off && !is.bad;
+    }
+}
+
+// fn(rows) for workgroup blk's mx_rows tiles (one, or a multiple of two)
+template <class Fn>
+__device__ __forceinline__ void mx_share(const SolverParams &sp, int32_t blk, int32_t halo, Fn &&fn) {
+    if (sp.mx_rows == 1) {
+        rows_from<1>(blk * kCellBlock, sp.n, halo, fn);
+    } else {
+        for (int32_t t = 0; t < sp.mx_rows; t += 2) {
+            const int64_t first = (static_cast<int64_t>(blk) * sp.mx_rows + t) * kCellBlock;
+            if (first < sp.n) rows_from<2>(static_cast<int32_t>(first), sp.n, halo, fn);
+        }
+    }
+}
+
+template <class Rows>
+struct RowsOf;
+template <int BS, int G, bool kIn>
+struct RowsOf<RowGroup<BS, G, kIn>> { static constexpr int value = G; };
+
+// the next direction, with the last iteration's y += alpha p, and q = As p; FP64
+// partial sums of p.q
+template <int kMode, class Lay>
+__device__ __forceinline__ void mx_direction_amul(int32_t blk, int32_t end, const SolverParams &sp, const Lay &L,
+                                                  const float *__restrict__ coef32, const float *__restrict__ r32,
+                                                  float *__restrict__ p32, float *__restrict__ p32b,
+                                                  float *__restrict__ d32, float *__restrict__ q32,
+                                                  double *__restrict__ part, PcgState *__restrict__ st) {
+    MxStep s;
+    if (!mx_take<kMode>(sp, blk == 0 && threadIdx.x == 0, part, st, s)) return;
+    end = min(end, sp.grid_mx);
+    const float *pl = s.cont ? (s.i & 1 ? p32 : p32b) : r32;     // without it beta is 0
+    float *pn = s.i & 1 ? p32b : p32;
+    const Dir2Vec<float> dir{r32, pl, s.gamma, s.beta};
+    for (; blk < end; ++blk) {
+        double acc[1] = {0.0};
+        mx_share(sp, blk, row_halo(L), [&](const auto &g) {
+            constexpr int R = RowsOf<std::decay_t<decltype(g)>>::value;
+            float rc[R], po[R], yc[R], pc[R], qc[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                rc[u] = g.at(r32, u);
+                po[u] = g.at(pl, u);
+                if (kMode == kMxNext) yc[u] = g.at(d32, u);
+            }
+            row_sums(L, g, coef32, dir, [&](int u) {
+                pc[u] = s.gamma * rc[u] + s.beta * po[u];
+                return pc[u];
+            }, qc);
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                g.set(pn, u, pc[u]);
+                g.set(q32, u, qc[u]);
+                if (kMode == kMxNext) g.set(d32, u, yc[u] + s.alpha * po[u]);
+                if (g.ok(u)) acc[0] += static_cast<double>(qc[u]) * static_cast<double>(pc[u]);
+            }
+        });
+        const int slots[1] = {kPartPq};
+        write_partials_at<1>(part, sp.grid, blk, slots, acc);
+    }
+}
+
+// k_mx_finalize<kMxAlpha>, then rs -= alpha q; FP64 partials of s|rs| and rs.rs
+__device__ __forceinline__ void mx_update_fold(int32_t blk, int32_t end, const SolverParams &sp, const float *__restrict__ q32,
+                                               const float *__restrict__ sig32, float *__restrict__ r32,
+                                               double *__restrict__ part, PcgState *__restrict__ st) {
+    if (group_inner_off(st)) return;
+    double v[1];
+    const int ps[1] = {kPartPq};
+    reduce_partials<1, kCellBlock, 4>(part, sp.grid, sp.grid_mx, ps, v);
+    const double pq = v[0], wArA = st->wArA;
+    const bool bad = !isfinite(pq), off = bad || !(fabs(pq) > 0.0);   // off: nothing left that FP32 can resolve
+    const double al = wArA / pq;
+    if (blk == 0 && threadIdx.x == 0) {
+        if (bad) {
+            st->nonfinite = 1;
+            st->done = 1;
+        } else if (off) {
+            st->inner_done = 1;
+        } else {
+            st->alpha = al;
+            st->wArA_prev = wArA;
+            st->n_iter_prev = st->n_iter;
+        }
+    }
+    if (off) return;
+    const float alpha = static_cast<float>(al);
+    end = min(end, sp.grid_mx);
+    for (; blk < end; ++blk) {
+        double acc[2] = {0.0, 0.0};
+        mx_share(sp, blk, 0, [&](const auto &g) {
+            constexpr int R = RowsOf<std::decay_t<decltype(g)>>::value;
+            float rc[R], qc[R], sc[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                rc[u] = g.at(r32, u);
+                qc[u] = g.at(q32, u);
+                sc[u] = g.at(sig32, u);
+            }
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                rc[u] -= alpha * qc[u];
+                g.set(r32, u, rc[u]);
+                if (g.ok(u)) {
+                    acc[0] += fabs(static_cast<double>(sc[u]) * static_cast<double>(rc[u]));
+                    acc[1] += static_cast<double>(rc[u]) * static_cast<double>(rc[u]);
+                }
+            }
+        });
+        const int slots[2] = {kPartSumR, kPartWr};
+        write_partials_at<2>(part, sp.grid, blk, slots, acc);
+    }
+}
+
+template <int kMode, class Lay>
+__global__ void __launch_bounds__(kCellBlock)
+k_mx_direction_amul(SolverParams sp, Lay L, const float *__restrict__ coef32, const float *__restrict__ r32,
+                    float *__restrict__ p32, float *__restrict__ p32b, float *__restrict__ d32,
+                    float *__restrict__ q32, double *__restrict__ part, PcgState *__restrict__ st) {
+    const int32_t b = static_cast<int32_t>(blockIdx.x);
+    mx_direction_amul<kMode>(b, b + 1, sp, L, coef32, r32, p32, p32b, d32, q32, part, st);
+}
+
+__global__ void __launch_bounds__(kCellBlock)
+k_mx_update_fold(SolverParams sp, const float *__restrict__ q32, const float *__restrict__ sig32,
+                 float *__restrict__ r32, double *__restrict__ part, PcgState *__restrict__ st) {
+    const int32_t b = static_cast<int32_t>(blockIdx.x);
+    mx_update_fold(b, b + 1, sp, q32, sig32, r32, part, st);
+}
+
+// ---------------------------------------------------------------------------
 // The inner iteration of several problems in one launch per kernel (a group:
 // lf_group_*).  Member i of a launch takes its workgroups gl.begin[i] ..
 // gl.begin[i+1] - 1, which run the same rows and write the same partials as
@@ -482,39 +750,34 @@ __global__ void __launch_bounds__(kFinBlock) k_mx_finalize(SolverParams sp, cons
 // per member.  Each problem's arithmetic and sums are therefore those of its
 // own launches, whatever else shares the launch.
 // ---------------------------------------------------------------------------
+template <int kMode>
 __global__ void __launch_bounds__(kCellBlock)
-k_grp_direction(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    mx_direction(b - gl.begin[i], m.sp, m.r32, m.p32, m.d32, m.st);
-}
-
-__global__ void __launch_bounds__(kCellBlock)
-k_grp_amul_dot(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    const int32_t blk = b - gl.begin[i];
-    with_member_layout(m, [&](auto L) { mx_amul_dot(blk, m.sp, L, m.coef32, m.p32, m.q32, m.part, m.st); });
+k_grp_direction_amul(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    with_member_layout(m, [&](auto L) {
+        mx_direction_amul<kMode>(s.share, s.end, m.sp, L, m.coef32, m.r32, m.p32, m.p32b, m.d32, m.q32, m.part, m.st);
+    });
 }
 
 __global__ void __launch_bounds__(kCellBlock)
 k_grp_update(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    mx_update(b - gl.begin[i], m.sp, m.q32, m.sig32, m.r32, m.part, m.st);
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    mx_update_fold(s.share, s.end, m.sp, m.q32, m.sig32, m.r32, m.part, m.st);
 }
 
 template <int Mode>
 __global__ void __launch_bounds__(kFinBlock) k_grp_finalize(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const MemberDesc &m = tab[gl.slot[blockIdx.x]];
+    const MemberDesc m = global_member(tab[gl.slot[blockIdx.x]]);
     mx_finalize<Mode>(m.sp, m.part, m.st);
 }
 
-// every member's solver state into out[slot]
+// every member's solver state into out[slot] (host memory the GPU can write)
 __global__ void k_grp_gather(const MemberDesc *__restrict__ tab, GroupLaunch gl, PcgState *__restrict__ out) {
     const int32_t i = static_cast<int32_t>(blockIdx.x);
     const int32_t n = static_cast<int32_t>(sizeof(PcgState) / sizeof(int32_t));
-    const int32_t *src = reinterpret_cast<const int32_t *>(tab[gl.slot[i]].st);
+    const int32_t *src = reinterpret_cast<const int32_t *>(as_global(tab[gl.slot[i]].st));
     int32_t *dst = reinterpret_cast<int32_t *>(out + gl.slot[i]);
     for (int32_t t = threadIdx.x; t < n; t += blockDim.x) dst[t] = src[t];
 }
@@ -523,26 +786,28 @@ __global__ void k_grp_gather(const MemberDesc *__restrict__ tab, GroupLaunch gl,
 // from each member's sp.grid; finalize: one workgroup per member)
 __global__ void __launch_bounds__(kCellBlock)
 k_grp_scale(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    const int32_t blk = b - gl.begin[i];
-    with_member_layout(m, [&](auto L) { mx_scale(blk, m.sp, L, m.sig32, m.coef, m.coef32w); });
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    with_member_layout(m, [&](auto L) {
+        for (int32_t b = s.share; b < min(s.end, m.sp.grid); ++b) mx_scale(b, m.sp, L, m.sig32, m.coef, m.coef32w);
+    });
 }
 
 __global__ void __launch_bounds__(kCellBlock)
 k_grp_correct(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    mx_correct(b - gl.begin[i], m.sp, m.T, m.d32, m.p32, m.sig32, m.st);
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    for (int32_t b = s.share; b < min(s.end, m.sp.grid); ++b)
+        mx_correct(b, m.sp, m.T, m.d32, m.p32, m.p32b, m.sig32, m.st);
 }
 
 __global__ void __launch_bounds__(kCellBlock)
 k_grp_residual(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    const int32_t blk = b - gl.begin[i];
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
     with_member_layout(m, [&](auto L) {
-        mx_residual(blk, m.sp, L, m.diagB, m.coef, m.srcB, m.T, m.p32, m.r32, m.d32, m.part, m.st);
+        for (int32_t b = s.share; b < min(s.end, m.sp.grid); ++b)
+            mx_residual(b, m.sp, L, m.diagB, m.coef, m.srcB, m.T, m.p32, m.p32b, m.r32, m.d32, m.part, m.st);
     });
 }
 
@@ -551,29 +816,40 @@ void launch_group_scale(const MemberDesc *tab, const GroupLaunch &cells, hipStre
                        cells);
 }
 
-void launch_group_pass_start(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s) {
-    hipLaunchKernelGGL(k_grp_finalize<kMxInnerStart>, dim3(static_cast<unsigned>(gl.n)), dim3(kFinBlock), 0, s,
-                       tab, gl);
+// the first direction and product of the members' solves (big: those whose
+// decisions the one-workgroup kernels take)
+void launch_group_solve_start(const MemberDesc *tab, const GroupLaunch &gl, const GroupLaunch &big, hipStream_t s) {
+    if (big.n) {
+        launch_group_fin_start(tab, big, s);
+        hipLaunchKernelGGL(k_grp_finalize<kMxInnerStart>, dim3(static_cast<unsigned>(big.n)), dim3(kFinBlock), 0, s,
+                           tab, big);
+    }
+    hipLaunchKernelGGL(k_grp_direction_amul<kMxSolve>, dim3(static_cast<unsigned>(gl.begin[gl.n])), dim3(kCellBlock),
+                       0, s, tab, gl);
 }
 
-// the end of a refinement pass: correction, FP64 residual, outer check
-void launch_group_pass_end(const MemberDesc *tab, const GroupLaunch &cells, hipStream_t s) {
+// the end of a refinement pass: correction, FP64 residual; then the outer check
+// and the next pass's first direction and product
+void launch_group_turn(const MemberDesc *tab, const GroupLaunch &cells, const GroupLaunch &inner,
+                       const GroupLaunch &big, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(cells.begin[cells.n]));
     hipLaunchKernelGGL(k_grp_correct, grid, dim3(kCellBlock), 0, s, tab, cells);
     hipLaunchKernelGGL(k_grp_residual, grid, dim3(kCellBlock), 0, s, tab, cells);
-    hipLaunchKernelGGL(k_grp_finalize<kMxOuter>, dim3(static_cast<unsigned>(cells.n)), dim3(kFinBlock), 0, s, tab,
-                       cells);
+    if (big.n) {
+        const dim3 each(static_cast<unsigned>(big.n));
+        hipLaunchKernelGGL(k_grp_finalize<kMxOuter>, each, dim3(kFinBlock), 0, s, tab, big);
+        hipLaunchKernelGGL(k_grp_finalize<kMxInnerStart>, each, dim3(kFinBlock), 0, s, tab, big);
+    }
+    hipLaunchKernelGGL(k_grp_direction_amul<kMxPass>, dim3(static_cast<unsigned>(inner.begin[inner.n])),
+                       dim3(kCellBlock), 0, s, tab, inner);
 }
 
-// one inner iteration of the launch's members (grid sizes from gl)
+// one inner iteration of the launch's members (grid sizes from gl): the update,
+// the next direction and its product
 void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s) {
-    const dim3 blk(kCellBlock), fin(kFinBlock), cells(static_cast<unsigned>(gl.begin[gl.n])),
-        each(static_cast<unsigned>(gl.n));
-    hipLaunchKernelGGL(k_grp_direction, cells, blk, 0, s, tab, gl);
-    hipLaunchKernelGGL(k_grp_amul_dot, cells, blk, 0, s, tab, gl);
-    hipLaunchKernelGGL(k_grp_finalize<kMxAlpha>, each, fin, 0, s, tab, gl);
-    hipLaunchKernelGGL(k_grp_update, cells, blk, 0, s, tab, gl);
-    hipLaunchKernelGGL(k_grp_finalize<kMxBeta>, each, fin, 0, s, tab, gl);
+    const dim3 cells(static_cast<unsigned>(gl.begin[gl.n]));
+    hipLaunchKernelGGL(k_grp_update, cells, dim3(kCellBlock), 0, s, tab, gl);
+    hipLaunchKernelGGL(k_grp_direction_amul<kMxNext>, cells, dim3(kCellBlock), 0, s, tab, gl);
 }
 
 void launch_group_gather(const MemberDesc *tab, const GroupLaunch &gl, PcgState *out, hipStream_t s) {
@@ -622,6 +898,7 @@ MemberDesc member_desc(const lf_problem *P) {
     m.sig32 = P->sig32;
     m.r32 = P->r32;
     m.p32 = P->p32;
+    m.p32b = P->p32b;
     m.d32 = P->d32;
     m.q32 = P->q32;
     m.part = P->part;
@@ -634,7 +911,27 @@ static void launch_mx_fin(lf_problem *P, hipStream_t s) {
     LF_LAUNCH(P, LF_K_FINALIZE, s, k_mx_finalize<Mode>, dim3(1), dim3(kFinBlock), 0, s, P->sp, P->part, P->state);
 }
 
+// two-launch form: the next direction and its product
+template <int kMode>
+static void launch_direction_amul(lf_problem *P, hipStream_t s) {
+    with_layout(P, [&](auto lay) {
+        using Lay = decltype(lay);
+        if constexpr (!std::is_same_v<Lay, RBLayout>) {
+            auto kern = k_mx_direction_amul<kMode, Lay>;
+            LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, kern, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, lay, P->coef32,
+                      P->r32, P->p32, P->p32b, P->d32, P->q32, P->part, P->state);
+        }
+    });
+}
+
 static void launch_inner_iteration(lf_problem *P, hipStream_t s) {
+    if (P->sp.mx_rows > 0) {
+        // the update of the product's iteration, then the next direction and product
+        LF_LAUNCH(P, LF_K_INNER_UPDATE, s, k_mx_update_fold, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->q32,
+                  P->sig32, P->r32, P->part, P->state);
+        launch_direction_amul<kMxNext>(P, s);
+        return;
+    }
     LF_LAUNCH(P, LF_K_INNER_DIRECTION, s, k_mx_direction, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->r32,
               P->p32, P->d32, P->state);
     with_layout(P, [&](auto lay) {
@@ -646,16 +943,10 @@ static void launch_inner_iteration(lf_problem *P, hipStream_t s) {
             }
         }
         constexpr int K = WalkBands<decltype(lay)>::value;
-        if constexpr (K > 0) {
-            if (P->walk) {
-                LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot_walk<K>,
-                          dim3(static_cast<unsigned>(P->sp.grid_mx_amul)), dim3(kCellBlock), 0, s, P->sp, lay,
-                          P->coef32, P->p32, P->q32, P->part, P->state);
-                return;
-            }
-        }
-        LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot<decltype(lay)>, mx_grid(P), dim3(kCellBlock), 0, s,
-                  P->sp, lay, P->coef32, P->p32, P->q32, P->part, P->state);
+        if constexpr (K > 0)
+            LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot_walk<K>,
+                      dim3(static_cast<unsigned>(P->sp.grid_mx_amul)), dim3(kCellBlock), 0, s, P->sp, lay,
+                      P->coef32, P->p32, P->q32, P->part, P->state);
     });
     launch_mx_fin<kMxAlpha>(P, s);
     LF_LAUNCH(P, LF_K_INNER_UPDATE, s, k_mx_update, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->q32, P->sig32,
@@ -772,14 +1063,23 @@ void launch_mx_scale(lf_problem *P, hipStream_t s) {
     });
 }
 
-// start of a refinement pass (rs, y = 0 and their partial sums were written
-// by the kernel that formed the FP64 residual: the assembly or k_mx_residual)
-static void launch_pass_start(lf_problem *P, hipStream_t s) { launch_mx_fin<kMxInnerStart>(P, s); }
+// start of a solve (kMxSolve) or of a later refinement pass (kMxPass) after its
+// rs, y = 0 and their partial sums (written by the kernel that formed the FP64
+// residual): the decisions and, in the two-launch form, the first direction and
+// product
+template <int kMode>
+static void launch_pass_start(lf_problem *P, hipStream_t s) {
+    const bool one_wg = !P->sp.mx_fold_start;
+    if (one_wg && kMode == kMxSolve) launch_fin<kFinStart>(P, s);
+    if (one_wg && kMode == kMxPass) launch_mx_fin<kMxOuter>(P, s);
+    if (one_wg) launch_mx_fin<kMxInnerStart>(P, s);
+    if (P->sp.mx_rows > 0) launch_direction_amul<kMode>(P, s);
+}
 
-// end of a pass: correction, true residual, outer decision
+// end of a pass: correction, true residual
 static void launch_pass_end(lf_problem *P, hipStream_t s) {
     LF_LAUNCH(P, LF_K_MIXED_CORRECT, s, k_mx_correct, cell_grid(P), dim3(kCellBlock), 0, s, P->sp, P->T, P->d32,
-              P->p32, P->sig32, P->state);
+              P->p32, P->p32b, P->sig32, P->state);
     with_layout(P, [&](auto lay) {
         if constexpr (std::is_same_v<decltype(lay), BandLayout<3>>) {
             if (P->box) {
@@ -799,9 +1099,8 @@ static void launch_pass_end(lf_problem *P, hipStream_t s) {
             }
         }
         LF_LAUNCH(P, LF_K_MIXED_RESIDUAL, s, k_mx_residual<decltype(lay)>, cell_grid(P), dim3(kCellBlock), 0, s,
-                  P->sp, lay, P->diagB, P->coef, P->srcB, P->T, P->p32, P->r32, P->d32, P->part, P->state);
+                  P->sp, lay, P->diagB, P->coef, P->srcB, P->T, P->p32, P->p32b, P->r32, P->d32, P->part, P->state);
     });
-    launch_mx_fin<kMxOuter>(P, s);
 }
 
 static lf_status get_inner_graph(lf_problem *P, int lg) {
@@ -857,8 +1156,7 @@ static int32_t predicted_inner(const lf_problem *P, int32_t pass) {
 lf_status mixed_start(lf_problem *P, SolveCtx &c) {
     hipStream_t s = P->stream;
     prof_lead(P, s);
-    launch_fin<kFinStart>(P, s);      // normFactor, res0 and the initial decision (shared with FP64)
-    launch_pass_start(P, s);
+    launch_pass_start<kMxSolve>(P, s);
     LF_HIP(hipGetLastError());
     c.fixed_k = P->prof_on ? 1 : P->opts.iters_per_check;
     c.k = c.fixed_k > 0 ? c.fixed_k : predicted_inner(P, 0);
@@ -886,6 +1184,9 @@ lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_sta
         out->nonfinite = h.nonfinite;
         out->n_outer = h.n_outer;
         P->last_outer = h.n_outer;
+        // without a walk the last residual left the sums of T (or, with no pass,
+        // the step's own are still there)
+        P->sumx_valid = P->sp.mx_rows > 0;
         *finished = true;
         return LF_OK;
     }
@@ -894,11 +1195,8 @@ lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_sta
         return LF_ESTATE;
     }
     if (c.stage == 1) {
-        // the outer check after a pass asked for another one
+        // the outer check after a pass asked for another one, and started it
         c.stage = 0;
-        prof_lead(P, s);
-        launch_pass_start(P, s);
-        LF_HIP(hipGetLastError());
         c.k = predicted_inner(P, h.n_outer);
         return mixed_block(P, c);
     }
@@ -907,20 +1205,19 @@ lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_sta
         if (adaptive) c.k = 2;
         return mixed_block(P, c);
     }
-    // pass finished: correct, check, and (unless it may have been the last one)
-    // start the next pass, all no-ops once the solve is done
+    // pass finished: correct, check and start the next pass (a no-op once the
+    // solve is done); its iterations follow unless it may have been the last one
     const int32_t pass = h.n_outer;
     if (pass < lf_problem::kPassTrack) P->last_inner[pass] = h.inner_iter;
     prof_lead(P, s);
     launch_pass_end(P, s);
+    launch_pass_start<kMxPass>(P, s);
     LF_HIP(hipGetLastError());
     if (adaptive && P->last_outer > 0 && pass + 1 >= P->last_outer) {
         c.stage = 1;
         c.k = 0;
         return mixed_block(P, c);
     }
-    launch_pass_start(P, s);
-    LF_HIP(hipGetLastError());
     if (adaptive) c.k = predicted_inner(P, pass + 1);
     return mixed_block(P, c);
 }

@@ -98,32 +98,36 @@ __device__ __forceinline__ void reset_state(PcgState *__restrict__ st, double x_
     st->inner_done = 0;
 }
 
+// The mean of x0 for the assembly: taken here by every workgroup from the sums'
+// partials (k_finalize<kFinMean>; lead: workgroup 0 resets the state), or read
+// where that kernel ran
+__device__ __forceinline__ double mean_of_x(const SolverParams &sp, bool lead, const double *__restrict__ part,
+                                            PcgState *__restrict__ st) {
+    if (sp.grid_sum == 0) return st->x_avg;
+    double v[1];
+    const int ps[1] = {kPartSumX};
+    reduce_partials<1, kCellBlock, 4>(part, sp.grid, sp.grid_sum, ps, v);
+    const double x_avg = v[0] / static_cast<double>(sp.n);
+    if (lead && threadIdx.x == 0) reset_state(st, x_avg);
+    return x_avg;
+}
+
 template <class Lay, bool kFull, bool kSetup, bool kMixed, bool kNonorth = false>
 __device__ __forceinline__ void assemble_rows(
-    int32_t blk, const SolverParams &sp, double rdt, double DT, const Lay &L, const int32_t *__restrict__ bface_start,
+    int32_t blk, double x_avg, const SolverParams &sp, double rdt, double DT, const Lay &L, const int32_t *__restrict__ bface_start,
     const int32_t *__restrict__ bface_list, const int32_t *__restrict__ bface_patch,
     const double *__restrict__ bmag_sf, const double *__restrict__ bdelta, const int32_t *__restrict__ patch_type,
     const double *__restrict__ patch_value, const double *__restrict__ V, const double *__restrict__ T,
     double *__restrict__ coef, double *__restrict__ upper, double *__restrict__ diag, double *__restrict__ source,
     double *__restrict__ diagB, double *__restrict__ srcB, double *__restrict__ int_coeff,
     double *__restrict__ bou_coeff, int32_t diag_pc, double *__restrict__ r, double *__restrict__ rD,
-    double *__restrict__ part, PcgState *__restrict__ st, float *__restrict__ sig32, float *__restrict__ r32,
+    double *__restrict__ part, float *__restrict__ sig32, float *__restrict__ r32,
     float *__restrict__ d32, double *__restrict__ p, const double *__restrict__ lap_src,
     const double *__restrict__ T_old, const double *__restrict__ nb_g = nullptr,
     const double *__restrict__ nb_gk = nullptr, double *__restrict__ xs = nullptr) {
     const int32_t c = blk * kCellBlock + static_cast<int32_t>(threadIdx.x);
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    double x_avg = 0.0;
-    if (kSetup && sp.grid_sum > 0) {
-        // the two-launch form: k_finalize<kFinMean> taken by every workgroup
-        double v[1];
-        const int ps[1] = {kPartSumX};
-        reduce_partials<1, kCellBlock, 4>(part, sp.grid, sp.grid_sum, ps, v);
-        x_avg = v[0] / static_cast<double>(sp.n);
-        if (blk == 0 && threadIdx.x == 0) reset_state(st, x_avg);
-    } else if (kSetup) {
-        x_avg = st->x_avg;
-    }
+
     if (c < sp.n) {
         RowCoefs<Lay> rcf;
         const double lap_diag = assemble_coefs<kFull>(L, c, DT, coef, upper, rcf);
@@ -222,10 +226,11 @@ k_assemble(SolverParams sp, double rdt, double DT, Lay L, const int32_t *__restr
            float *__restrict__ r32, float *__restrict__ d32, double *__restrict__ p,
            const double *__restrict__ lap_src, const double *__restrict__ T_old,
            const double *__restrict__ nb_g, const double *__restrict__ nb_gk, double *__restrict__ xs) {
+    const double x_avg = kSetup ? mean_of_x(sp, blockIdx.x == 0, part, st) : 0.0;
     assemble_rows<Lay, kFull, kSetup, kMixed, kNonorth>(
-        sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x), sp, rdt, DT, L, bface_start, bface_list, bface_patch, bmag_sf, bdelta,
+        sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x), x_avg, sp, rdt, DT, L, bface_start, bface_list, bface_patch, bmag_sf, bdelta,
         patch_type, patch_value, V, T, coef, upper, diag, source, diagB, srcB, int_coeff, bou_coeff, diag_pc, r, rD,
-        part, st, sig32, r32, d32, p, lap_src, T_old, nb_g, nb_gk, xs);
+        part, sig32, r32, d32, p, lap_src, T_old, nb_g, nb_gk, xs);
 }
 
 // partial sums of x0 = T (its mean enters the normalisation factor)
@@ -1861,35 +1866,43 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(SolverParams sp, const d
 // workgroups gl.begin[i] .. (its own cell grid) or workgroup i (finalize).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(kCellBlock) k_grp_sum_x(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    sum_x_rows(b - gl.begin[i], m.sp, m.T, m.part);
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    for (int32_t b = s.share; b < min(s.end, m.sp.grid); ++b) sum_x_rows(b, m.sp, m.T, m.part);
 }
 
 template <int Mode>
 __global__ void __launch_bounds__(kFinBlock) k_grp_fin(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const MemberDesc &m = tab[gl.slot[blockIdx.x]];
+    const MemberDesc m = global_member(tab[gl.slot[blockIdx.x]]);
     finalize_state<Mode>(m.sp, m.part, m.st);
 }
 
 __global__ void __launch_bounds__(kCellBlock) k_grp_assemble(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x), i = group_member(gl, b);
-    const MemberDesc &m = tab[gl.slot[i]];
-    const int32_t blk = b - gl.begin[i];
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    const double x_avg = mean_of_x(m.sp, s.lead, m.part, m.st);
     with_member_layout(m, [&](auto L) {
-        assemble_rows<decltype(L), false, true, true>(blk, m.sp, m.rdt, m.DT, L, m.bface_start, m.bface_list,
-                                                      m.bface_patch, m.bmag_sf, m.bdelta, m.patch_type,
-                                                      m.patch_value, m.V, m.T, m.coef, nullptr, nullptr, nullptr,
-                                                      m.diagB, m.srcB, nullptr, nullptr, m.diag_pc, m.r, m.rD,
-                                                      m.part, m.st, m.sig32, m.r32, m.d32, m.p, nullptr, nullptr);
+        for (int32_t b = s.share; b < min(s.end, m.sp.grid); ++b)
+            assemble_rows<decltype(L), false, true, true>(b, x_avg, m.sp, m.rdt, m.DT, L, m.bface_start, m.bface_list,
+                                                          m.bface_patch, m.bmag_sf, m.bdelta, m.patch_type,
+                                                          m.patch_value, m.V, m.T, m.coef, nullptr, nullptr, nullptr,
+                                                          m.diagB, m.srcB, nullptr, nullptr, m.diag_pc, m.r, m.rD,
+                                                          m.part, m.sig32, m.r32, m.d32, m.p, nullptr, nullptr);
     });
 }
 
-void launch_group_setup(const MemberDesc *tab, const GroupLaunch &cells, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>(cells.begin[cells.n]));
-    hipLaunchKernelGGL(k_grp_sum_x, grid, dim3(kCellBlock), 0, s, tab, cells);
-    hipLaunchKernelGGL(k_grp_fin<kFinMean>, dim3(static_cast<unsigned>(cells.n)), dim3(kFinBlock), 0, s, tab, cells);
-    hipLaunchKernelGGL(k_grp_assemble, grid, dim3(kCellBlock), 0, s, tab, cells);
+// sums: members whose sums of T have to be taken; means: those whose mean the
+// one-workgroup kernel takes
+void launch_group_setup(const MemberDesc *tab, const GroupLaunch &cells, const GroupLaunch &sums,
+                        const GroupLaunch &means, hipStream_t s) {
+    if (sums.n)
+        hipLaunchKernelGGL(k_grp_sum_x, dim3(static_cast<unsigned>(sums.begin[sums.n])), dim3(kCellBlock), 0, s, tab,
+                           sums);
+    if (means.n)
+        hipLaunchKernelGGL(k_grp_fin<kFinMean>, dim3(static_cast<unsigned>(means.n)), dim3(kFinBlock), 0, s, tab,
+                           means);
+    hipLaunchKernelGGL(k_grp_assemble, dim3(static_cast<unsigned>(cells.begin[cells.n])), dim3(kCellBlock), 0, s, tab,
+                       cells);
 }
 
 void launch_group_fin_start(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s) {
@@ -2056,7 +2069,7 @@ lf_status launch_assemble_setup(lf_problem *P, hipStream_t s) {
             LF_LAUNCH(P, LF_K_SETUP1, s, k_sum_x, cell_grid(P), dim3(kCellBlock), 0, s, P->sp, P->T, P->part);
     }
     P->sumx_valid = false;
-    if (!P->fold) launch_fin<kFinMean>(P, s);
+    if (P->sp.grid_sum == 0) launch_fin<kFinMean>(P, s);     // else taken by the assembly
     if (P->opts.precision == LF_PREC_MIXED) {
         launch_assemble_t<false, true, true>(P, s);
         launch_mx_scale(P, s);

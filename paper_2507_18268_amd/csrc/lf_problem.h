@@ -50,6 +50,10 @@ struct PcgState {
     double wArA_prev;
     int32_t n_iter_prev;
     int32_t conv_prev;
+    // precision form, two launches per inner iteration: n_outer, inner_iter and
+    // wArA as the residual at a pass end found them (wArA in wArA_prev)
+    int32_t n_outer_prev;
+    int32_t inner_iter_prev;
 };
 
 // Block walk of a box's band layout (the tiles, lanes and rows are described
@@ -95,6 +99,13 @@ constexpr int kFoldRows = 2;
 // up to this many rows its workgroups take contiguous shares per die: 100^3
 // 22.6 -> 20.2 us per product, 128^3 38.2 -> 38.5
 constexpr int32_t kFoldDieRows = 3 << 19;
+// The precision form's inner iteration without a walk: rows per thread such that
+// the partials per slot stay at most 2048 to 8 M rows (one row per thread, for
+// more workgroups, on small meshes); the start of a pass sums one partial per
+// 512 rows and four slots in every workgroup, which is too many above
+// kMxFoldStartRows, and the mean of x0 one slot above kMxFoldMeanRows.
+constexpr int32_t kMxOneRow = 1 << 18, kMxFoldStartRows = 2 << 20, kMxFoldMeanRows = 1 << 20;
+constexpr int kMxManyRows = 8;
 // the block walk's solves above this many partials per slot run on the
 // Jacobi-scaled matrix
 constexpr int32_t kScaledPartials = 512;
@@ -104,7 +115,10 @@ struct SolverParams {
     int32_t max_iter, min_iter;
     int32_t n;            // cells
     int32_t grid;         // workgroups of a cell-parallel launch (= partials per slot)
-    int32_t grid_mx;      // workgroups of an FP32 inner-solve launch (kMxRows rows per thread)
+    int32_t grid_mx;      // workgroups of an FP32 inner-solve launch (mx_rows or kMxRows rows per thread)
+    int32_t mx_rows;      // precision form without a walk: two launches per inner iteration, this many
+                          // rows per thread; else 0
+    int32_t mx_fold_start;// and the decisions at the start of a pass taken in the first of them
     int32_t n_red;        // DIC: first black cell
     int32_t max_outer;    // mixed: refinement passes cap
     int32_t grid_amul;    // workgroups of the FP64 Amul launch (= its p.q partials)
@@ -190,6 +204,7 @@ struct lf_problem {
     float *coef32 = nullptr, *diag32 = nullptr, *rD32 = nullptr;
     float *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr;
     double *bic = nullptr, *bbc = nullptr;     // [B] batched kernel: boundary coefficients by boundary list position
+    float *p32b = nullptr;                     // two-launch form: directions alternate between p32 and this
     float *sig32 = nullptr;                    // multi-kernel precision form: sqrt(diagB) in FP32
     // host side
     lf::PcgState *h_state = nullptr;           // pinned

@@ -98,11 +98,13 @@ lf_status launch_amul_inner_hook(lf_problem *P, const float *x, float *y);
 MemberDesc member_desc(const lf_problem *P);
 // launches over the members of gl (cells: each member's sp.grid workgroups;
 // inner: its sp.grid_mx; finalize: one per member)
-void launch_group_setup(const MemberDesc *tab, const GroupLaunch &cells, hipStream_t s);
+void launch_group_setup(const MemberDesc *tab, const GroupLaunch &cells, const GroupLaunch &sums,
+                        const GroupLaunch &means, hipStream_t s);
 void launch_group_scale(const MemberDesc *tab, const GroupLaunch &cells, hipStream_t s);
 void launch_group_fin_start(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s);
-void launch_group_pass_start(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s);
-void launch_group_pass_end(const MemberDesc *tab, const GroupLaunch &cells, hipStream_t s);
+void launch_group_solve_start(const MemberDesc *tab, const GroupLaunch &inner, const GroupLaunch &big, hipStream_t s);
+void launch_group_turn(const MemberDesc *tab, const GroupLaunch &cells, const GroupLaunch &inner,
+                       const GroupLaunch &big, hipStream_t s);
 void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &inner, hipStream_t s);
 void launch_group_gather(const MemberDesc *tab, const GroupLaunch &gl, PcgState *out, hipStream_t s);
 // non-orthogonal meshes: boundary values and gradient of T, then (correction:
