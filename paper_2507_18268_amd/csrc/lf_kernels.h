@@ -19,11 +19,44 @@ __device__ __forceinline__ T *as_global(T *p) {
     return (T *)(__attribute__((address_space(1))) T *)reinterpret_cast<uintptr_t>(p);
 }
 
+// v of another lane by a DPP move (every lane of the wavefront active)
+template <int Ctrl>
+__device__ __forceinline__ double dpp_lane(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), Ctrl, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), Ctrl, 0xf, 0xf, false));
+}
+
+// v summed with the other 32-lane half's (kRow = 32) or the neighbouring row of
+// 16's: the swap instruction given v twice returns each pair's first lanes in
+// one register and its second lanes in the other
+template <int kRow>
+__device__ __forceinline__ double pair_sum(double v) {
+    const unsigned lo = static_cast<unsigned>(__double2loint(v)), hi = static_cast<unsigned>(__double2hiint(v));
+    if constexpr (kRow == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double(static_cast<int>(h[0]), static_cast<int>(l[0])) +
+               __hiloint2double(static_cast<int>(h[1]), static_cast<int>(l[1]));
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double(static_cast<int>(h[0]), static_cast<int>(l[0])) +
+               __hiloint2double(static_cast<int>(h[1]), static_cast<int>(l[1]));
+    }
+}
+
 // Sum over a wavefront of 64 lanes by xor butterflies; every lane ends with the
-// same value because each pairwise sum is commutative.
+// same value because each pairwise sum is commutative.  The exchanges stay in
+// the vector unit (a shuffle goes through the LDS, a hundred cycles per level):
+// rotations of a row of 16 by 8 and 4 are the xor exchanges there, since the
+// values then repeat every 8 lanes.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = pair_sum<32>(v);
+    v = pair_sum<16>(v);
+    v += dpp_lane<0x128>(v);      // row_ror:8
+    v += dpp_lane<0x124>(v);      // row_ror:4
+    v += dpp_lane<0x4e>(v);       // quad_perm [2,3,0,1]
+    v += dpp_lane<0xb1>(v);       // quad_perm [1,0,3,2]
     return v;
 }
 
