@@ -195,6 +195,7 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
                 P->box32 = true;
                 P->bw32 = bw32;
                 P->sp.grid_mx_amul = bw32.blocks;
+                if (opts.precision == LF_PREC_MIXED) P->sp.grid_mx = vec4_blocks(m->N);
             }
         }
     }

@@ -158,6 +158,82 @@ k_mx_direction(SolverParams sp, const float *__restrict__ r32, float *__restrict
     mx_direction(walk_share((st->inner_iter & 1) != 0), sp, r32, p32, d32, st);
 }
 
+// The vector kernels of the block walk's solve (x-lines of a multiple of four
+// cells, so N is one too): four adjacent rows per 16-byte access, kVec4 of them
+// per thread.  One row per 4-byte access held them at 5.0 (update) and 6.4 TB/s.
+constexpr int kVec4 = 2;
+__device__ __forceinline__ int64_t vec4_row(int32_t blk, int j) {
+    return 4 * static_cast<int64_t>(cell_row_at<kVec4>(blk, j));
+}
+__device__ __forceinline__ void lanes_store(float *__restrict__ a, int64_t i, const Lanes<float, 4> &r) {
+    *reinterpret_cast<Lanes<float, 4>::vec *>(a + i) = Lanes<float, 4>::vec{r.v[0], r.v[1], r.v[2], r.v[3]};
+}
+
+// mx_direction
+__global__ void __launch_bounds__(kCellBlock)
+k_mx_direction4(SolverParams sp, const float *__restrict__ r32, float *__restrict__ p32, float *__restrict__ d32,
+                const PcgState *__restrict__ st) {
+    if (inner_off(st)) return;
+    typedef Lanes<float, 4> R;
+    const int32_t blk = walk_share((st->inner_iter & 1) != 0);
+    const bool first = st->inner_iter == 0, cont = st->inner_cont != 0;
+    const float beta = static_cast<float>(st->beta), alpha = static_cast<float>(st->alpha),
+                gamma = static_cast<float>(st->gamma);
+#pragma unroll
+    for (int j = 0; j < kVec4; ++j) {
+        const int64_t c = vec4_row(blk, j);
+        if (c >= sp.n) continue;
+        const R rc = lanes_load<float, 4>(r32, c);
+        R pn = rc;
+        if (!first || cont) {
+            const R pc = lanes_load<float, 4>(p32, c);
+            if (first) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) pn.v[w] = gamma * rc.v[w] + beta * pc.v[w];
+            } else {
+                // y is next needed an iteration later: stream it past the caches
+                R y = lanes_load<float, 4, true>(d32, c);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    y.v[w] = y.v[w] + alpha * pc.v[w];
+                    pn.v[w] = rc.v[w] + beta * pc.v[w];
+                }
+                lanes_store_stream(d32, c, y);
+            }
+        }
+        lanes_store(p32, c, pn);
+    }
+}
+
+// mx_update
+__global__ void __launch_bounds__(kCellBlock)
+k_mx_update4(SolverParams sp, const float *__restrict__ q32, const float *__restrict__ sig32,
+             float *__restrict__ r32, double *__restrict__ part, const PcgState *__restrict__ st) {
+    if (inner_off(st)) return;
+    typedef Lanes<float, 4> R;
+    const int32_t blk = walk_share((st->inner_iter & 1) != 0);
+    const float alpha = static_cast<float>(st->alpha);
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kVec4; ++j) {
+        const int64_t c = vec4_row(blk, j);
+        if (c >= sp.n) continue;
+        const R qc = lanes_load<float, 4, true>(q32, c);
+        const R sc = lanes_load<float, 4>(sig32, c);
+        R rc = lanes_load<float, 4>(r32, c);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            rc.v[w] = rc.v[w] - alpha * qc.v[w];
+            const double rd = static_cast<double>(rc.v[w]);
+            acc[0] += fabs(static_cast<double>(sc.v[w]) * rd);
+            acc[1] += rd * rd;
+        }
+        lanes_store(r32, c, rc);
+    }
+    const int slots[2] = {kPartSumR, kPartWr};
+    write_partials_at<2>(part, sp.grid, blk, slots, acc);
+}
+
 // q = As p in FP32 (unit diagonal: p_c first, then the row's entries in order)
 // by the row walk (band layouts with two or more bands), FP64 partial sums of p.q:
 // sp.grid_mx_amul workgroups, whose partials fill the start of the p.q slot
@@ -332,10 +408,10 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
     if (st->done) return;
     const bool keep = st->inner_iter > 0;
     const int32_t blk = walk_share(true);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     typedef Lanes<double, 2> R;
     typedef float F2 __attribute__((ext_vector_type(2)));
-    box_walk<double, 2, true, false>(blk, L, bw, diagB, coef, T, [&](int64_t c, const R &ax, const R &, const R &db) {
+    box_walk<double, 2, true, false>(blk, L, bw, diagB, coef, T, [&](int64_t c, const R &ax, const R &xc, const R &db) {
         // the two rows as pass_end_row takes them, with 16- and 8-byte accesses
         const R b = lanes_load<double, 2>(srcB, c);
         const F2 pp = keep ? *reinterpret_cast<const F2 *>(p32 + c) : F2{0.0f, 0.0f};
@@ -344,6 +420,7 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
         for (int w = 0; w < 2; ++w) {
             const double rc = b.v[w] - ax.v[w];
             acc[0] += fabs(rc);
+            acc[4] += xc.v[w];          // the sum of x0 for the next solve's mean
             const double sg = static_cast<float>(sqrt(db.v[w]));
             const float rs = static_cast<float>(rc / sg);
             rs2[w] = rs;
@@ -354,8 +431,11 @@ k_mx_residual_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__
         *reinterpret_cast<F2 *>(r32 + c) = rs2;
         *reinterpret_cast<F2 *>(d32 + c) = F2{0.0f, 0.0f};
     });
-    const int slots[4] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32};
-    write_partials_at<4, kBwBlock>(part, sp.grid, blk, slots, acc);
+    // the mean is taken from one partial per 512 rows: zeros in those past the walk's
+    if (threadIdx.x == 0)
+        for (int32_t s = bw.blocks + blk; s < sp.grid; s += bw.blocks) part[kPartSumX * sp.grid + s] = 0.0;
+    const int slots[5] = {kPartSumR, kPartSumR32, kPartWr32, kPartRp32, kPartSumX};
+    write_partials_at<5, kBwBlock>(part, sp.grid, blk, slots, acc);
 }
 
 // The start of an inner solve from the sums v of s|rs|, rs.rs and rs.p.
@@ -932,8 +1012,12 @@ static void launch_inner_iteration(lf_problem *P, hipStream_t s) {
         launch_direction_amul<kMxNext>(P, s);
         return;
     }
-    LF_LAUNCH(P, LF_K_INNER_DIRECTION, s, k_mx_direction, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->r32,
-              P->p32, P->d32, P->state);
+    if (P->box32)
+        LF_LAUNCH(P, LF_K_INNER_DIRECTION, s, k_mx_direction4, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->r32,
+                  P->p32, P->d32, P->state);
+    else
+        LF_LAUNCH(P, LF_K_INNER_DIRECTION, s, k_mx_direction, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->r32,
+                  P->p32, P->d32, P->state);
     with_layout(P, [&](auto lay) {
         if constexpr (std::is_same_v<decltype(lay), BandLayout<3>>) {
             if (P->box32) {
@@ -949,8 +1033,12 @@ static void launch_inner_iteration(lf_problem *P, hipStream_t s) {
                       P->coef32, P->p32, P->q32, P->part, P->state);
     });
     launch_mx_fin<kMxAlpha>(P, s);
-    LF_LAUNCH(P, LF_K_INNER_UPDATE, s, k_mx_update, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->q32, P->sig32,
-              P->r32, P->part, P->state);
+    if (P->box32)
+        LF_LAUNCH(P, LF_K_INNER_UPDATE, s, k_mx_update4, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->q32, P->sig32,
+                  P->r32, P->part, P->state);
+    else
+        LF_LAUNCH(P, LF_K_INNER_UPDATE, s, k_mx_update, mx_grid(P), dim3(kCellBlock), 0, s, P->sp, P->q32, P->sig32,
+                  P->r32, P->part, P->state);
     launch_mx_fin<kMxBeta>(P, s);
 }
 
@@ -1184,9 +1272,9 @@ lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_sta
         out->nonfinite = h.nonfinite;
         out->n_outer = h.n_outer;
         P->last_outer = h.n_outer;
-        // without a walk the last residual left the sums of T (or, with no pass,
-        // the step's own are still there)
-        P->sumx_valid = P->sp.mx_rows > 0;
+        // the last residual left the sums of T (or, with no pass, the step's own are
+        // still there); the row walk's does not
+        P->sumx_valid = P->sp.mx_rows > 0 || P->box;
         *finished = true;
         return LF_OK;
     }

@@ -12,6 +12,8 @@ inline int32_t mx_blocks(int32_t n) {
     return n > 0 ? (n + kTile - 1) / kTile : 1;
 }
 inline dim3 mx_grid(const lf_problem *P) { return dim3(static_cast<unsigned>(P->sp.grid_mx)); }
+// workgroups of the FP32 vector kernels that take two groups of four rows per thread
+inline int32_t vec4_blocks(int32_t n) { return (n - 1) / (8 * kCellBlock) + 1; }
 // workgroups of the FP64 update with the diagonal preconditioner
 inline int32_t update_blocks(int32_t n) {
     constexpr int32_t kTile = kCellBlock * kUpdRows;
