@@ -87,8 +87,9 @@ typedef int32_t lf_status;
                               else one row per thread; the FP64 products of a
                               box then take the block walk
                               (lf_problem_amul_walk), and so they do on any
-                              box that gives the block walk at least 2048
-                              workgroups of 256 threads (4.2 M cells and up) */
+                              box that gives the block walk enough workgroups
+                              of 256 threads: 1200 (2.5 M cells and up) in
+                              LF_PREC_FP64, 3600 (7.4 M) in LF_PREC_MIXED */
 #define LF_WALK_ON 1       /* the row walk whenever the layout allows it (tests) */
 #define LF_WALK_OFF 2      /* always one row per thread */
 
@@ -331,8 +332,8 @@ lf_status lf_problem_layout(const lf_problem *problem, int32_t *layout);
 /* How the problem's FP64 matrix-vector products run: 0 one row per thread,
  * 1 the row walk, 2 the block walk of a box (a band layout with offsets 1, nx,
  * nx ny, nx even and N even, whenever the row walk is chosen for it or the
- * block walk has at least 2048 workgroups: two x-adjacent rows per lane, two
- * lines by two planes per thread).  With 2 the
+ * block walk has the workgroups LF_WALK_AUTO asks for: two x-adjacent rows per
+ * lane, two lines by two planes per thread).  With 2 the
  * inner FP32 products of LF_PREC_MIXED take the block walk too when nx is a
  * multiple of 4 (four rows per lane), else the row walk; with 1 the row walk.
  * 3: DIC on the two-colour band layout with x-lines of a multiple of four
@@ -472,7 +473,8 @@ lf_status lf_batch_stats(lf_batch *batch, lf_solve_stats *stats, double *elapsed
 
 /* ---- grouped form --------------------------------------------------------
  * Several LF_PREC_MIXED problems (diagonal preconditioner, orthogonal meshes,
- * FP64 products one row per thread: lf_problem_amul_walk reports 0) stepped
+ * FP64 products one row per thread: lf_problem_amul_walk reports 0; boxes below
+ * 4.2 M cells) stepped
  * together, for many mid-size problems at once, each too small to fill the
  * GPU (the serving stream's large requests): every kernel of their steps runs
  * as one launch for all members that need it at that point (each member keeps

@@ -179,7 +179,9 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
         const int32_t wb = walk_blocks(m->N, m->band_d[1]);
         BoxWalk bw, bw32;
         const bool box_plan = box_walk_plan(m->N, m->n_bands, m->band_d, 2, &bw);
-        if ((opts.amul_walk == LF_WALK_ON || wb >= kWalkMinBlocks || (box_plan && bw.blocks >= kBoxMinBlocks)) &&
+        P->too_large = wb >= kWalkMinBlocks || (box_plan && bw.blocks >= kGroupBoxBlocks);
+        const int32_t min_blocks = opts.precision == LF_PREC_MIXED ? kBoxMinBlocksMixed : kBoxMinBlocks;
+        if ((opts.amul_walk == LF_WALK_ON || wb >= kWalkMinBlocks || (box_plan && bw.blocks >= min_blocks)) &&
             wb <= P->sp.grid_mx) {
             P->walk = true;
             P->sp.grid_amul = wb;

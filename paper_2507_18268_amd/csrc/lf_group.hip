@@ -95,8 +95,9 @@ lf_status check_member(const lf_group *g, const lf_problem *P) {
     if (P->opts.precision != LF_PREC_MIXED) { set_error("a group runs LF_PREC_MIXED problems"); return LF_EINVAL; }
     if (P->opts.precond != LF_PC_DIAGONAL) { set_error("a group runs the diagonal preconditioner"); return LF_EINVAL; }
     if (P->nonorth) { set_error("a group runs orthogonal meshes (no corrector loop)"); return LF_EINVAL; }
-    if (P->walk || P->box || P->rb || P->sp.mx_rows <= 0) {
-        set_error("a group runs the one-row-per-thread products (lf_problem_amul_walk 0)");
+    if (P->walk || P->box || P->rb || P->too_large || P->sp.mx_rows <= 0) {
+        set_error("a group runs the one-row-per-thread products (lf_problem_amul_walk 0) of meshes that do not fill the GPU "
+                  "by themselves");
         return LF_EINVAL;
     }
     if (P->mesh->device != g->device) {

@@ -64,10 +64,16 @@ struct PcgState {
 constexpr int bw_lines(int) { return 2; }
 constexpr int bw_planes(int W) { return W == 2 ? 2 : 1; }
 constexpr int kBwBlock = 256;       // threads of a block-walk workgroup
-// a box takes the block walk from this many of its workgroups (4.2 M cells and
-// up) whatever the row walk's workgroup count
-constexpr int kBoxMinBlocks = 2048;
-
+// A box takes the block walk from this many of its workgroups (2048 rows each)
+// whatever the row walk's workgroup count.  FP64: from 2.5 M rows, where the two
+// launches' vectors outgrow the last-level cache (five steps of the graded box,
+// two launches or, above 2.6 M rows, one row per thread against the walk's scaled
+// solve: 130^3 3.53 / 3.60 ms, 136^3 4.14 / 4.00, 150^3 5.77 / 5.42, 160^3
+// 7.08 / 6.51).  Precision form: from 7.4 M rows (168^3 6.70 / 7.10 ms, 184^3
+// 8.13 / 8.74, 200^3 11.95 both, 220^3 17.3 / 15.0).
+constexpr int kBoxMinBlocks = 1200, kBoxMinBlocksMixed = 3600;
+// boxes from this many block-walk workgroups are too large for a group's member
+constexpr int kGroupBoxBlocks = 2048;
 // host-side plan of a block walk with W x-adjacent rows per lane
 struct BoxWalk {
     int32_t hx;        // threads per tile (nx / W)
@@ -92,9 +98,11 @@ inline bool box_walk_plan(int32_t n, int32_t K, const int32_t *d, int32_t W, Box
 
 constexpr int kMaxGraphLog = 6;   // largest captured block: 64 iterations
 // FP64 solves with the diagonal preconditioner and no walk run two launches per
-// iteration up to this many rows, one row per thread up to kFoldOneRow, else
+// iteration up to this many rows (their vectors then just fit the 256 MB
+// last-level cache: 140^3 4.47 against 4.55 ms in five launches, 160^3 8.35
+// against 7.08), one row per thread up to kFoldOneRow, else
 // kFoldRows in the product
-constexpr int32_t kFoldMaxRows = 2 << 20, kFoldOneRow = 1 << 19;
+constexpr int32_t kFoldMaxRows = 5 << 19, kFoldOneRow = 1 << 19;
 constexpr int kFoldRows = 2;
 // up to this many rows its workgroups take contiguous shares per die: 100^3
 // 22.6 -> 20.2 us per product, 128^3 38.2 -> 38.5
@@ -166,6 +174,7 @@ struct lf_problem {
     bool rb = false;                           // coefficients in the two-colour band layout (DIC)
     bool walk = false;                         // FP64 Amul by the row walk (bands >= 2, large meshes)
     bool box = false;                          // FP64 products by the block walk (box band layouts, with walk)
+    bool too_large = false;                    // for a group: a band mesh that fills the GPU by itself
     lf::BoxWalk bw{};                          // its plan (2 rows per lane)
     bool box32 = false;                        // the FP32 inner product too (mixed; 4 rows per lane)
     lf::BoxWalk bw32{};
