@@ -294,6 +294,44 @@ __device__ __forceinline__ int64_t die_block(unsigned b, unsigned nb) {
 
 __device__ __forceinline__ bool is_face(const Rec &r) { return r.x != 0.0 || r.y != 0.0 || r.z != 0.0; }
 
+// Which share of the cells workgroup blockIdx.x takes: contiguous runs per die
+// while that saves more re-reads than it costs in streaming (with the stores by
+// lines: 100^3 28.0 against 31.8 us, 128^3 66.6 / 70.2, 160^3 123.9 / 119.9, 192^3
+// 205.3 / 201.2).
+constexpr int64_t kGradDieCells = 3 << 20;
+__device__ __forceinline__ int64_t grad_share(int32_t n) {
+    return n <= kGradDieCells ? die_block(blockIdx.x, gridDim.x) : static_cast<int64_t>(blockIdx.x);
+}
+
+// The gradient of cell c to its xyz row, past the caches.  A wavefront's 64 rows
+// are 1536 contiguous bytes, but one store per component writes every third
+// double of them: three partial writes of each line (192^3 213 us).  Where the
+// wavefront holds 64 consecutive cells it passes them through the LDS and
+// writes 512 bytes per store (205 us).
+__device__ __forceinline__ void store_rows(double *__restrict__ grad, int64_t c, double gx, double gy, double gz) {
+    __shared__ double tile[kGradBlock / 64][3 * 64];
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    double *t = tile[threadIdx.x >> 6];
+    const int first = static_cast<int>(c) - lane;
+    if (__ballot(first == __builtin_amdgcn_readfirstlane(first)) == ~0ull) {
+        t[3 * lane] = gx;
+        t[3 * lane + 1] = gy;
+        t[3 * lane + 2] = gz;
+        // the wavefront's own LDS writes and reads complete in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double *o = grad + 3 * (c - lane);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) __builtin_nontemporal_store(t[64 * i + lane], o + 64 * i + lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __builtin_nontemporal_store(gx, grad + 3 * c);
+        __builtin_nontemporal_store(gy, grad + 3 * c + 1);
+        __builtin_nontemporal_store(gz, grad + 3 * c + 2);
+    }
+}
+
 // Band-form meshes: the faces of cell c are the band slots k*N + c (owned,
 // neighbour c + d_k) and k*N + c - d_k (lower, owner c - d_k); a slot with a
 // zero area vector holds no face (real faces have |S_f| > 0).  The lower
@@ -319,7 +357,7 @@ k_grad_band(int32_t n, BandOffsets bo, const double *__restrict__ T, const doubl
             const double *__restrict__ gbface, const double *__restrict__ V, double *__restrict__ grad,
             double *__restrict__ bgrad) {
     const int64_t D = bo.d[K - 1];
-    const int64_t g = die_block(blockIdx.x, gridDim.x) * kGradBlock + threadIdx.x;
+    const int64_t g = grad_share(n) * kGradBlock + threadIdx.x;
     const int64_t chunk = g / D;
     int64_t c = chunk * R * D + (g - chunk * D);
     if (c >= n) return;
@@ -384,9 +422,7 @@ k_grad_band(int32_t n, BandOffsets bo, const double *__restrict__ T, const doubl
             grad[n + c] = gy;
             grad[2 * static_cast<int64_t>(n) + c] = gz;
         } else {
-            __builtin_nontemporal_store(gx, grad + 3 * c);
-            __builtin_nontemporal_store(gy, grad + 3 * c + 1);
-            __builtin_nontemporal_store(gz, grad + 3 * c + 2);
+            store_rows(grad, c, gx, gy, gz);
         }
         if (bgrad) {
             for (int32_t k = b0; k < b1; ++k) {
