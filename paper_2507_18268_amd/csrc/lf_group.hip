@@ -72,7 +72,8 @@ struct lf_group {
     hipStream_t stream = nullptr;
     int32_t max_members = 0, iters = 2;
     lf::MemberDesc *d_tab = nullptr, *h_tab = nullptr;
-    lf::PcgState *h_states = nullptr;   // pinned: the gather writes it
+    lf::PcgState *h_states = nullptr;   // pinned: the gather writes it (d_hstates: its address there)
+    lf::PcgState *d_hstates = nullptr;
     std::vector<lf::GroupMember> members;
     hipEvent_t ev_block = nullptr;
     bool in_flight = false;
@@ -266,7 +267,7 @@ lf_status launch_next(lf_group *g) {
     if (!inner.empty()) {
         gi = launch_of(g, inner, inner_blocks);
         for (int32_t k = 0; k < g->iters; ++k) launch_group_iteration(g->d_tab, gi, st);
-        launch_group_gather(g->d_tab, gi, g->h_states, st);
+        launch_group_gather(g->d_tab, gi, g->d_hstates, st);
     }
     LF_HIP(hipGetLastError());
     LF_HIP(hipEventRecord(g->ev_block, st));
@@ -322,6 +323,7 @@ lf_status lf_group_create(int32_t max_members, int32_t iters_per_block, void *ws
                                            hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&g->h_states), sizeof(PcgState) * max_members,
                                            hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&g->d_hstates), g->h_states, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->ev_block, hipEventDisableTiming);
     if (e != hipSuccess) {
         set_error("group set-up failed: %s", hipGetErrorString(e));

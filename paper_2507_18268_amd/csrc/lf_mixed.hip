@@ -1229,7 +1229,8 @@ static lf_status mixed_block(lf_problem *P, SolveCtx &c) {
     prof_lead(P, s);
     LF_TRY(launch_inner(P, c.k));
     c.launched += c.k;
-    LF_HIP(hipMemcpyAsync(P->h_state, P->state, sizeof(PcgState), hipMemcpyDeviceToHost, s));
+    launch_publish(P, s);
+    LF_HIP(hipGetLastError());
     LF_HIP(hipEventRecord(P->ev[2], s));
     return LF_OK;
 }

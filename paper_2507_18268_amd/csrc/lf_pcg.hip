@@ -602,12 +602,26 @@ k_sum_x_fold(SolverParams sp, const double *__restrict__ T, double *__restrict__
     write_partials<1>(part, sp.grid, slots, acc);
 }
 
+// The solver state for the host, written by workgroup 0 into pinned memory
+// (hst; null: not asked for), which it reads once the event behind the launch
+// has completed
+__device__ __forceinline__ void publish_state(const PcgState *__restrict__ st, PcgState *__restrict__ hst) {
+    if (!hst || blockIdx.x != 0) return;
+    constexpr int kWords = static_cast<int>(sizeof(PcgState) / sizeof(int32_t));
+    const int32_t *src = reinterpret_cast<const int32_t *>(st);
+    int32_t *dst = reinterpret_cast<int32_t *>(hst);
+    for (int i = static_cast<int>(threadIdx.x); i < kWords; i += static_cast<int>(blockDim.x)) dst[i] = src[i];
+}
+
+__global__ void k_publish(const PcgState *__restrict__ st, PcgState *__restrict__ hst) { publish_state(st, hst); }
+
 // k_commit for the two-launch form: the last direction's buffer by the
 // iteration count, R rows per thread
 template <int R>
 __global__ void __launch_bounds__(kCellBlock)
 k_commit_fold(SolverParams sp, double *__restrict__ x, const double *__restrict__ p0, const double *__restrict__ p1,
-              double *__restrict__ part, const PcgState *__restrict__ st) {
+              double *__restrict__ part, const PcgState *__restrict__ st, PcgState *__restrict__ hst) {
+    publish_state(st, hst);
     if (!st->done) return;
     const bool apply = !(st->n_iter < 1 || st->singular || st->nonfinite);
     const double alpha = st->alpha;
@@ -640,7 +654,8 @@ k_commit_fold(SolverParams sp, double *__restrict__ x, const double *__restrict_
 // same values), which the next solve's mean takes instead of a pass of its own.
 __global__ void __launch_bounds__(kCellBlock)
 k_commit(SolverParams sp, double *__restrict__ x, const double *__restrict__ p, double *__restrict__ part,
-         const PcgState *__restrict__ st) {
+         const PcgState *__restrict__ st, PcgState *__restrict__ hst) {
+    publish_state(st, hst);
     if (!st->done) return;
     const bool apply = !(st->n_iter < 1 || st->singular || st->nonfinite);
     const double alpha = st->alpha;
@@ -794,7 +809,8 @@ k_direction_scaled(SolverParams sp, const double *__restrict__ r, double *__rest
 __global__ void __launch_bounds__(kCellBlock)
 k_commit_scaled(SolverParams sp, double *__restrict__ T, const double *__restrict__ xs,
                 const double *__restrict__ p, const double *__restrict__ sd, double *__restrict__ part,
-                const PcgState *__restrict__ st) {
+                const PcgState *__restrict__ st, PcgState *__restrict__ hst) {
+    publish_state(st, hst);
     if (!st->done) return;
     const bool moved = st->n_iter >= 1;
     const bool apply = !(st->n_iter < 1 || st->singular || st->nonfinite);
@@ -1918,12 +1934,11 @@ __global__ void k_spin(int64_t ticks) {
     while (wall_clock64() - t0 < ticks) __builtin_amdgcn_s_sleep(8);
 }
 
-__global__ void k_any_nonfinite(const double *__restrict__ a, int32_t n, PcgState *st) {
+// *flag (pinned host memory) = 1 if a value is not finite
+__global__ void k_any_nonfinite(const double *__restrict__ a, int32_t n, int32_t *flag) {
     int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n && !isfinite(a[i])) atomicOr(&st->flag, 1);
+    if (i < n && !isfinite(a[i])) *flag = 1;
 }
-
-__global__ void k_clear_flag(PcgState *st) { st->flag = 0; }
 
 // test hook: the solver state "not done", so that the preconditioner's kernels run
 __global__ void k_clear_done(PcgState *st) { st->done = 0; }
@@ -2344,17 +2359,22 @@ static lf_status launch_iterations(lf_problem *P, int32_t k) {
 }
 
 // block of k iterations, then the state copy and ev[2]
-// end of a solve (does nothing while the solve is not done)
-static void launch_commit(lf_problem *P, hipStream_t s) {
+// end of a solve (does nothing while the solve is not done); hst: where the
+// state goes for the host, or null
+static void launch_commit(lf_problem *P, hipStream_t s, PcgState *hst) {
     if (P->scaled)
         LF_LAUNCH(P, LF_K_COMMIT, s, k_commit_scaled, cell_grid(P), dim3(kCellBlock), 0, s, P->sp, P->T, P->w,
-                  P->p, P->rD, P->part, P->state);
+                  P->p, P->rD, P->part, P->state, hst);
     else if (P->fold)
         LF_LAUNCH(P, LF_K_COMMIT, s, k_commit_fold<kUpdRows>, dim3(static_cast<unsigned>(P->sp.grid_sum)),
-                  dim3(kCellBlock), 0, s, P->sp, P->T, P->p, P->p2, P->part, P->state);
+                  dim3(kCellBlock), 0, s, P->sp, P->T, P->p, P->p2, P->part, P->state, hst);
     else
         LF_LAUNCH(P, LF_K_COMMIT, s, k_commit, cell_grid(P), dim3(kCellBlock), 0, s, P->sp, P->T, P->p, P->part,
-                  P->state);
+                  P->state, hst);
+}
+
+void launch_publish(lf_problem *P, hipStream_t s) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, P->state, P->d_hstate);
 }
 
 static lf_status fp64_block(lf_problem *P, SolveCtx &c) {
@@ -2365,9 +2385,9 @@ static lf_status fp64_block(lf_problem *P, SolveCtx &c) {
     c.launched += c.k;
     // the commit follows in the same block, so that the host waits once per
     // block and not again after it (the timing runs launch it when it is due)
-    if (!P->prof_on) launch_commit(P, s);
+    if (!P->prof_on) launch_commit(P, s, P->d_hstate);
+    else launch_publish(P, s);
     LF_HIP(hipGetLastError());
-    LF_HIP(hipMemcpyAsync(P->h_state, P->state, sizeof(PcgState), hipMemcpyDeviceToHost, s));
     LF_HIP(hipEventRecord(P->ev[2], s));
     return LF_OK;
 }
@@ -2377,7 +2397,7 @@ lf_status fp64_start(lf_problem *P, SolveCtx &c) {
     prof_lead(P, s);
     LF_TRY(launch_setup(P, s));
     c.fixed_k = P->prof_on ? 1 : P->opts.iters_per_check;
-    c.k = c.fixed_k > 0 ? c.fixed_k : std::max<int32_t>(1, P->last_iters > 0 ? P->last_iters + 1 : 8);
+    c.k = c.fixed_k > 0 ? c.fixed_k : P->last_iters > 0 ? P->last_iters : 8;
     c.launched = 0;
     c.stage = 0;
     return fp64_block(P, c);
@@ -2390,7 +2410,7 @@ lf_status fp64_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_stat
     const PcgState &h = *P->h_state;
     if (h.done && P->prof_on && c.stage == 0) {
         prof_lead(P, s);
-        launch_commit(P, s);
+        launch_commit(P, s, nullptr);
         LF_HIP(hipGetLastError());
         LF_HIP(hipEventRecord(P->ev[2], s));
         c.stage = 1;
@@ -2412,7 +2432,8 @@ lf_status fp64_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_stat
         set_error("solver state never reached done after %d iterations", c.launched);
         return LF_ESTATE;
     }
-    if (c.fixed_k <= 0) c.k = std::max<int32_t>(2, c.k / 2);
+    // the counts repeat from step to step, give or take one; a first solve doubles
+    if (c.fixed_k <= 0) c.k = P->last_iters > 0 ? std::max<int32_t>(2, c.launched / 8) : c.launched;
     return fp64_block(P, c);
 }
 
@@ -2477,11 +2498,10 @@ lf_status launch_amul_hook(lf_problem *P, const double *x, double *y) {
 
 lf_status check_finite_device(lf_problem *P, const double *T, bool *ok) {
     const int32_t N = P->mesh->N;
-    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, P->stream, P->state);
+    P->h_state->flag = 0;      // no work that writes it is in flight
     hipLaunchKernelGGL(k_any_nonfinite, dim3((N + kBlock - 1) / kBlock), dim3(kBlock), 0, P->stream, T, N,
-                       P->state);
+                       &P->d_hstate->flag);
     LF_HIP(hipGetLastError());
-    LF_HIP(hipMemcpyAsync(P->h_state, P->state, sizeof(PcgState), hipMemcpyDeviceToHost, P->stream));
     LF_HIP(hipStreamSynchronize(P->stream));
     *ok = P->h_state->flag == 0;
     return LF_OK;

@@ -36,7 +36,7 @@ struct PcgState {
     int32_t converged;
     int32_t singular;
     int32_t nonfinite;
-    int32_t flag;         // scratch flag (input checks)
+    int32_t flag;         // scratch flag (input checks; the host copy's only)
     // mixed precision: inner FP32 solve of one refinement pass
     double inner_target;  // stop when the inner residual's L1 norm <= this
     int32_t inner_done;
@@ -216,7 +216,8 @@ struct lf_problem {
     float *p32b = nullptr;                     // two-launch form: directions alternate between p32 and this
     float *sig32 = nullptr;                    // multi-kernel precision form: sqrt(diagB) in FP32
     // host side
-    lf::PcgState *h_state = nullptr;           // pinned
+    lf::PcgState *h_state = nullptr;           // pinned; kernels write it (d_hstate: its address for them)
+    lf::PcgState *d_hstate = nullptr;
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     hipStream_t capture_stream = nullptr;
     hipGraphExec_t g_iter[lf::kMaxGraphLog + 1] = {};   // 2^i PCG iterations

@@ -133,6 +133,8 @@ lf_status mixed_start(lf_problem *P, SolveCtx &c);
 lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_stats *out);
 lf_status launch_amul_hook(lf_problem *P, const double *x, double *y);
 lf_status launch_precondition_hook(lf_problem *P);
+// the solver state into the host's copy (P->h_state)
+void launch_publish(lf_problem *P, hipStream_t s);
 lf_status check_finite_device(lf_problem *P, const double *T, bool *ok);
 
 }  // namespace lf
