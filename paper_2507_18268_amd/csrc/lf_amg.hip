@@ -35,7 +35,7 @@ constexpr int32_t kAmgMinSide = 3;    // nor one with a side shorter than this
 // on smaller levels, whose launches are latency-bound, the one-row kernels
 // finish sooner)
 constexpr int32_t kAmgWalkMinBlocks = 1024;
-static_assert(kAmgNu >= 1 && kAmgNuC >= 2, "level 0's last sweep must not be its first");
+static_assert(kAmgNu == 2 && kAmgNuC == 4, "the launches pair the first two sweeps; the LDS cycle alternates two iterates");
 
 struct AmgBox {
     int32_t nx, ny, nz;
@@ -53,6 +53,7 @@ static std::vector<AmgBox> amg_boxes(const lf_mesh *m) {
 }
 
 static void plan_amg_walks(lf_problem *P);
+static void plan_amg_tail(lf_problem *P);
 
 void carve_amg(Carver &cv, const lf_mesh *m, lf_problem *P) {
     const std::vector<AmgBox> boxes = amg_boxes(m);
@@ -78,6 +79,7 @@ void carve_amg(Carver &cv, const lf_mesh *m, lf_problem *P) {
         P->amg_t1 = t1;
         P->amg_t2 = t2;
         plan_amg_walks(P);
+        plan_amg_tail(P);
     }
 }
 
@@ -92,87 +94,54 @@ static BandLayout<3> box_layout(int32_t nx, int32_t ny, int32_t nz) {
     return L;
 }
 
-// first sweep, from x = 0 (A x = 0): x = 0 + omega ((b - 0) / diag)
-__global__ void __launch_bounds__(kCellBlock)
-k_amg_first(int32_t n, const double *__restrict__ b, const double *__restrict__ diag, double *__restrict__ x,
-            const PcgState *__restrict__ st) {
-    if (st->done) return;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
-    if (c < n) x[c] = 0.0 + kAmgOmega * ((b[c] - 0.0) / diag[c]);
+// The residual b - A x summed over the cells (ascending) of coarse cell t / 8,
+// by eight neighbouring lanes: lane t % 8 forms one cell's residual, and every
+// lane adds the eight in order (a cell past the end of an odd side adds 0 to a
+// sum that is never -0).  One thread per coarse cell ran its eight rows one
+// after the other in an eighth of the wavefronts: 35.6 us for the three
+// launches at 100^3, 50^3 and 25^3 cells, against 23.5.  All lanes of a wave
+// call it together; past the last coarse cell (t >= 8 cn) the result is unused.
+__device__ __forceinline__ double amg_block_residual(const BandLayout<3> &F, int32_t fnx, int32_t fny, int32_t fnz,
+                                                     int32_t cnx, int32_t cny, int32_t cn, int32_t t,
+                                                     const double *__restrict__ diag,
+                                                     const double *__restrict__ coef, const double *__restrict__ b,
+                                                     const double *__restrict__ x) {
+    const int32_t I = t >> 3;
+    const int32_t ix = I % cnx, iy = (I / cnx) % cny, iz = I / (cnx * cny);
+    const int32_t fx = 2 * ix + (t & 1), fy = 2 * iy + ((t >> 1) & 1), fz = 2 * iz + ((t >> 2) & 1);
+    double r = 0.0;
+    if (I < cn && fx < fnx && fy < fny && fz < fnz) {
+        const int32_t c = fx + fnx * (fy + fny * fz);
+        const double dc = diag[c], bc = b[c];
+        const double ax = layout_dot(F, c, coef, x, dc * x[c]);
+        r = bc - ax;
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc += __shfl(r, k, 8);
+    return acc;
 }
 
-// y = x + omega ((b - A x) / diag), A x with the diagonal term first; kDot
-// (level 0's last sweep, y = w, b = r): also the partial sums of w.r
-template <bool kDot>
-__global__ void __launch_bounds__(kCellBlock)
-k_amg_sweep(SolverParams sp, BandLayout<3> L, const double *__restrict__ diag, const double *__restrict__ coef,
-            const double *__restrict__ b, const double *__restrict__ x, double *__restrict__ y,
-            double *__restrict__ part, const PcgState *__restrict__ st) {
-    if (st->done) return;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
-    double acc[1] = {0.0};
-    if (c < L.n) {
-        const double dc = diag[c], xc = x[c], bc = b[c];
-        const double ax = layout_dot(L, c, coef, x, dc * xc);
-        const double v = xc + kAmgOmega * ((bc - ax) / dc);
-        y[c] = v;
-        acc[0] = v * bc;
-    }
-    if (kDot) {
-        const int slots[1] = {kPartWr};
-        write_partials<1>(part, sp.grid, slots, acc);
-    }
-}
-
-// coarse right side: per block, the residual b - A x of its cells (ascending)
+// coarse right side
 __global__ void __launch_bounds__(kCellBlock)
 k_amg_restrict(BandLayout<3> F, int32_t fnx, int32_t fny, int32_t fnz, const double *__restrict__ diag,
                const double *__restrict__ coef, const double *__restrict__ b, const double *__restrict__ x,
                int32_t cnx, int32_t cny, int32_t cn, double *__restrict__ bc, const PcgState *__restrict__ st) {
     if (st->done) return;
-    const int32_t I = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
-    if (I >= cn) return;
-    const int32_t ix = I % cnx, iy = (I / cnx) % cny, iz = I / (cnx * cny);
-    double acc = 0.0;
-    for (int e = 0; e < 2; ++e) {
-        const int32_t fz = 2 * iz + e;
-        if (fz >= fnz) break;
-        for (int bb = 0; bb < 2; ++bb) {
-            const int32_t fy = 2 * iy + bb;
-            if (fy >= fny) break;
-            for (int a = 0; a < 2; ++a) {
-                const int32_t fx = 2 * ix + a;
-                if (fx >= fnx) break;
-                const int32_t c = fx + fnx * (fy + fny * fz);
-                const double dc = diag[c];
-                const double ax = layout_dot(F, c, coef, x, dc * x[c]);
-                acc += b[c] - ax;
-            }
-        }
-    }
-    bc[I] = acc;
-}
-
-// x += the coarse result of the cell's block
-__global__ void __launch_bounds__(kCellBlock)
-k_amg_prolong(int32_t fnx, int32_t fny, int32_t fn, int32_t cnx, int32_t cny, double *__restrict__ x,
-              const double *__restrict__ xc, const PcgState *__restrict__ st) {
-    if (st->done) return;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
-    if (c >= fn) return;
-    const int32_t fx = c % fnx, fy = (c / fnx) % fny, fz = c / (fnx * fny);
-    x[c] += xc[fx / 2 + cnx * (fy / 2 + cny * (fz / 2))];
+    const int32_t t = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
+    const double acc = amg_block_residual(F, fnx, fny, fnz, cnx, cny, cn, t, diag, coef, b, x);
+    if ((t & 7) == 0 && (t >> 3) < cn) bc[t >> 3] = acc;
 }
 
 // ---------------------------------------------------------------------------
-// The same steps by the block walk of a box level (x-lines of even length: two
-// rows per lane, 2 lines x 2 planes per thread, as the solver's product): each
-// row's A x is the one-row kernels' sum term for term, so every result is
-// bitwise the same.
+// Where a sweep takes x from: the level's iterate (MemX), the first sweep's
+// values or the iterate with the coarse correction added, formed on the fly, so
+// that a level's six launches (sweep, sweep, residual, correction, sweep,
+// sweep) are four: below about 100 k rows each costs 4.6 us whatever it does
+// (a step of the solve at 48^3 cells 2.73 ms with six, 2.20 with four).
 // ---------------------------------------------------------------------------
 
-// the first sweep's values (x = 0 + omega (b - 0) / diag), formed where the
-// walk asks for x
+// the first sweep's values (x = 0 + omega (b - 0) / diag)
 struct AmgFirstX {
     const double *__restrict__ b;
     const double *__restrict__ diag;
@@ -205,9 +174,8 @@ __device__ __forceinline__ int64_t fdiv(int64_t i, const FastDiv &f) {
     return static_cast<int64_t>((static_cast<uint64_t>(i) * f.m) >> f.sh);
 }
 
-// the prolonged iterate x + (the coarse result of the cell's block), formed
-// where the walk asks for x (a lane's two cells lie in one block: x-lines of
-// even length)
+// the prolonged iterate x + (the coarse result of the cell's block); vec: a
+// lane's two cells lie in one block (the walk's x-lines have even length)
 struct AmgProlongX {
     const double *__restrict__ x;
     const double *__restrict__ xc;
@@ -227,6 +195,168 @@ struct AmgProlongX {
     __device__ __forceinline__ double one(int64_t i) const { return x[i] + xc[block(i)]; }
 };
 
+// A x of row c, the diagonal term first (layout_dot's order), x from the source
+template <class XS>
+__device__ __forceinline__ double amg_row(const BandLayout<3> &L, int32_t c, const double *__restrict__ coef,
+                                          const XS &x, double acc) {
+    double a[6], xv[6];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int k = 2 - j;
+        const bool ok = c >= L.d[k];
+        const int32_t col = ok ? c - L.d[k] : c;
+        const double v = coef[static_cast<int64_t>(k) * L.n + col];
+        a[j] = ok ? v : 0.0;
+        xv[j] = x.one(col);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int32_t col = c < L.n - L.d[k] ? c + L.d[k] : c;
+        a[3 + k] = coef[static_cast<int64_t>(k) * L.n + c];
+        xv[3 + k] = x.one(col);
+    }
+#pragma unroll
+    for (int j = 0; j < 6; ++j) acc += a[j] * xv[j];
+    return acc;
+}
+
+// y = x + omega ((b - A x) / diag), A x with the diagonal term first, one row
+// per thread; kDot (level 0's last sweep, y = w, b = r): also the partial sums
+// of w.r.  Bound by the launch (4.6 us) up to about 100 k rows.
+template <class XS, bool kDot>
+__global__ void __launch_bounds__(kCellBlock)
+k_amg_sweep(SolverParams sp, BandLayout<3> L, const double *__restrict__ diag, const double *__restrict__ coef,
+            const double *__restrict__ b, XS x, double *__restrict__ y, double *__restrict__ part,
+            const PcgState *__restrict__ st) {
+    if (st->done) return;
+    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
+    double acc[1] = {0.0};
+    if (c < L.n) {
+        const double dc = diag[c], xc = x.one(c), bc = b[c];
+        const double ax = amg_row(L, c, coef, x, dc * xc);
+        const double v = xc + kAmgOmega * ((bc - ax) / dc);
+        y[c] = v;
+        acc[0] = v * bc;
+    }
+    if (kDot) {
+        const int slots[1] = {kPartWr};
+        write_partials<1>(part, sp.grid, slots, acc);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The last levels of the cycle in one workgroup: what is left of the cycle from
+// the first level on whose matrices and vectors, with those of all levels below
+// it, fit into the LDS (56 bytes a row: 2852 rows, 13 x 13 x 13 and 7 x 7 x 7
+// under a 200 x 200 x 200 box).  Bound by the chain of its passes: 19.7 us for
+// those two levels, whose seven launches take 4.7 us each; a step of the solve
+// at 48^3 cells 2.20 ms without, 1.94 ms with it, at 130^3 9.85 and 9.52.
+// Every value is formed as by the launches it replaces, so each result is
+// bitwise the same.
+// ---------------------------------------------------------------------------
+constexpr int kTailBlock = 1024;
+constexpr int kTailLevels = 4;
+constexpr int64_t kTailRows = (156 << 10) / (7 * static_cast<int64_t>(sizeof(double)));
+
+struct AmgTail {
+    int32_t count;
+    int32_t nx[kTailLevels], ny[kTailLevels], nz[kTailLevels];
+    int32_t off[kTailLevels];   // rows of the levels above, of the tail
+    const double *coef[kTailLevels], *diag[kTailLevels];
+    const double *b;
+    double *x;
+};
+
+__global__ void __launch_bounds__(kTailBlock)
+k_amg_tail(AmgTail T, const PcgState *__restrict__ st) {
+    if (st->done) return;
+    extern __shared__ double tail_mem[];
+    const int32_t tid = static_cast<int32_t>(threadIdx.x);
+    // the arrays of level l: the three bands, diag, b, and the two iterates
+    auto at = [&](int32_t l, int32_t n, int which) { return tail_mem + 7 * T.off[l] + static_cast<int32_t>(which) * n; };
+    auto rows = [&](int32_t l) { return T.nx[l] * T.ny[l] * T.nz[l]; };
+    auto layout = [&](int32_t l) {
+        BandLayout<3> L;
+        L.n = rows(l);
+        L.d[0] = 1;
+        L.d[1] = T.nx[l];
+        L.d[2] = T.nx[l] * T.ny[l];
+        L.mag_sf = nullptr;
+        L.delta = nullptr;
+        return L;
+    };
+    for (int32_t l = 0; l < T.count; ++l) {
+        const int32_t n = rows(l);
+        double *m = at(l, n, 0);
+        for (int32_t i = tid; i < 3 * n; i += kTailBlock) m[i] = T.coef[l][i];
+        for (int32_t i = tid; i < n; i += kTailBlock) m[3 * n + i] = T.diag[l][i];
+    }
+    {
+        const int32_t n = rows(0);
+        double *b = at(0, n, 4);
+        for (int32_t i = tid; i < n; i += kTailBlock) b[i] = T.b[i];
+    }
+    __syncthreads();
+    auto first = [&](int32_t l) {   // into the first iterate
+        const int32_t n = rows(l);
+        const double *dg = at(l, n, 3), *b = at(l, n, 4);
+        double *y = at(l, n, 5);
+        for (int32_t c = tid; c < n; c += kTailBlock) y[c] = 0.0 + kAmgOmega * ((b[c] - 0.0) / dg[c]);
+        __syncthreads();
+    };
+    auto sweep = [&](int32_t l, int from, int to) {
+        const BandLayout<3> L = layout(l);
+        const int32_t n = L.n;
+        const double *coef = at(l, n, 0), *dg = at(l, n, 3), *b = at(l, n, 4), *x = at(l, n, from);
+        double *y = at(l, n, to);
+        for (int32_t c = tid; c < n; c += kTailBlock) {
+            const double dc = dg[c], xc = x[c], bc = b[c];
+            const double ax = amg_row(L, c, coef, MemX<double, 2>{x}, dc * xc);
+            y[c] = xc + kAmgOmega * ((bc - ax) / dc);
+        }
+        __syncthreads();
+    };
+    const int32_t last = T.count - 1;
+    for (int32_t l = 0; l < last; ++l) {
+        first(l);
+        sweep(l, 5, 6);
+        const BandLayout<3> F = layout(l);
+        const int32_t n = F.n, fnx = T.nx[l], fny = T.ny[l], fnz = T.nz[l], cn = rows(l + 1);
+        const double *coef = at(l, n, 0), *dg = at(l, n, 3), *b = at(l, n, 4), *x = at(l, n, 6);
+        double *cb = at(l + 1, cn, 4);
+        for (int32_t t0 = 0; t0 < 8 * cn; t0 += kTailBlock) {
+            const int32_t t = t0 + tid;
+            const double acc = amg_block_residual(F, fnx, fny, fnz, T.nx[l + 1], T.ny[l + 1], cn, t, dg, coef, b, x);
+            if ((t & 7) == 0 && (t >> 3) < cn) cb[t >> 3] = acc;
+        }
+        __syncthreads();
+    }
+    first(last);
+    for (int k = 1; k < kAmgNuC; ++k) sweep(last, k % 2 ? 5 : 6, k % 2 ? 6 : 5);
+    for (int32_t l = last - 1; l >= 0; --l) {
+        const int32_t n = rows(l), fnx = T.nx[l], fny = T.ny[l], cnx = T.nx[l + 1], cny = T.ny[l + 1];
+        const double *xc = at(l + 1, rows(l + 1), 6);
+        double *x = at(l, n, 6);
+        for (int32_t c = tid; c < n; c += kTailBlock) {
+            const int32_t fx = c % fnx, fy = (c / fnx) % fny, fz = c / (fnx * fny);
+            x[c] += xc[fx / 2 + cnx * (fy / 2 + cny * (fz / 2))];
+        }
+        __syncthreads();
+        sweep(l, 6, 5);
+        sweep(l, 5, 6);
+    }
+    const int32_t n = rows(0);
+    const double *x = at(0, n, 6);
+    for (int32_t c = tid; c < n; c += kTailBlock) T.x[c] = x[c];
+}
+
+// ---------------------------------------------------------------------------
+// The same steps by the block walk of a box level (x-lines of even length: two
+// rows per lane, 2 lines x 2 planes per thread, as the solver's product): each
+// row's A x is the one-row kernels' sum term for term, so every result is
+// bitwise the same.
+// ---------------------------------------------------------------------------
+
 // y = x + omega ((b - A x) / diag) with x from the source: the level's
 // iterate, (AmgFirstX) the first sweep's values, so that the launch does the
 // level's first two sweeps, or (AmgProlongX) the iterate with the coarse
@@ -242,7 +372,8 @@ k_amg_sweep_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__re
     if (st->done) return;
     typedef Lanes<double, 2> R;
     double acc[1] = {0.0};
-    box_walk_xs<double, 2, false, false>(static_cast<int32_t>(blockIdx.x), L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &xc, const R &dg) {
+    const int32_t blk = walk_share(kDot);
+    box_walk_xs<double, 2, false, false>(blk, L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &xc, const R &dg) {
         const R bc = lanes_load<double, 2>(b, c);
         R v;
 #pragma unroll
@@ -255,7 +386,7 @@ k_amg_sweep_box(SolverParams sp, BandLayout<3> L, BoxWalk bw, const double *__re
     });
     if (kDot) {
         const int slots[1] = {kPartWr};
-        write_partials<1, kBwBlock>(part, sp.grid, slots, acc);
+        write_partials_at<1, kBwBlock>(part, sp.grid, blk, slots, acc);
         if (threadIdx.x == 0)
             for (int64_t j = bw.blocks + static_cast<int64_t>(blockIdx.x); j < sp.grid; j += bw.blocks)
                 part[static_cast<int64_t>(kPartWr) * sp.grid + j] = 0.0;
@@ -271,29 +402,29 @@ k_amg_restrict_box(BandLayout<3> L, BoxWalk bw, const double *__restrict__ diag,
                    const PcgState *__restrict__ st) {
     if (st->done) return;
     typedef Lanes<double, 2> R;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBwBlock + threadIdx.x;
-    R res[2][2];
-    // the walk visits a tile's rows line by line, within a line plane by plane
+    const int32_t blk = walk_share(true);
+    const int64_t i = static_cast<int64_t>(blk) * kBwBlock + threadIdx.x;
+    // the walk visits a tile's rows line by line, within a line plane by plane:
+    // the second plane of the first line waits for the first of the second
+    double acc = 0.0, h0 = 0.0, h1 = 0.0;
     int call = 0;
-    box_walk<double, 2, false, false>(static_cast<int32_t>(blockIdx.x), L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &, const R &) {
+    box_walk<double, 2, false, false>(blk, L, bw, diag, coef, x, [&](int64_t c, const R &ax, const R &, const R &) {
         const R bb = lanes_load<double, 2>(b, c);
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                if (2 * jj + kk == call)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) res[jj][kk].v[w] = bb.v[w] - ax.v[w];
+        const double r0 = bb.v[0] - ax.v[0], r1 = bb.v[1] - ax.v[1];
+        if (call == 1) {
+            h0 = r0;
+            h1 = r1;
+        } else {
+            acc += r0;
+            acc += r1;
+        }
+        if (call == 2) {
+            acc += h0;
+            acc += h1;
+        }
         ++call;
     });
     if (i >= static_cast<int64_t>(bw.ntiles) * bw.hx) return;
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) acc += res[bb][e].v[a];
     bc[i] = acc;
 }
 
@@ -369,6 +500,26 @@ static void plan_amg_walks(lf_problem *P) {
     }
 }
 
+// the first level whose cycle runs in one workgroup (0: none).  LF_WALK_ON
+// keeps the launches, so that the walk runs on every level that allows it.
+static void plan_amg_tail(lf_problem *P) {
+    const size_t levels = P->amg.size() + 1;
+    int64_t rows = 0;
+    size_t first = 0;
+    for (size_t l = levels; l-- > 1 && levels - l <= static_cast<size_t>(kTailLevels);) {
+        rows += P->amg[l - 1].n;
+        if (rows > kTailRows) break;
+        first = l;
+    }
+    P->amg_tail = 0;
+    if (first == 0 || P->opts.amul_walk == LF_WALK_ON) return;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_amg_tail), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            156 << 10) == hipSuccess)
+        P->amg_tail = first;
+    else
+        (void)hipGetLastError();
+}
+
 static dim3 grid_for(int64_t n) {
     return dim3(static_cast<unsigned>(std::max<int64_t>(1, (n + kCellBlock - 1) / kCellBlock)));
 }
@@ -396,90 +547,84 @@ void launch_amg_galerkin(lf_problem *P, hipStream_t s) {
     }
 }
 
+static const double *amg_tail(lf_problem *P, size_t l, const double *b, hipStream_t s) {
+    AmgTail T{};
+    int32_t rows = 0;
+    for (size_t k = l; k <= P->amg.size(); ++k) {
+        const AmgLevel &a = P->amg[k - 1];
+        const int32_t i = T.count++;
+        T.nx[i] = a.nx;
+        T.ny[i] = a.ny;
+        T.nz[i] = a.nz;
+        T.off[i] = rows;
+        T.coef[i] = a.coef;
+        T.diag[i] = a.diag;
+        rows += a.n;
+    }
+    T.b = b;
+    T.x = P->amg[l - 1].xa;
+    const size_t lds = 7 * sizeof(double) * static_cast<size_t>(rows);
+    LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, k_amg_tail, dim3(1), dim3(kTailBlock), static_cast<unsigned>(lds), s, T,
+              P->state);
+    return T.x;
+}
+
+// One sweep of level v into dst, x from the source, by the block walk where the
+// level has one; dot: with the w.r partials (level 0's last sweep).
+template <class XS>
+static void launch_sweep(lf_problem *P, const AmgView &v, const BandLayout<3> &L, bool walk, const BoxWalk &bw,
+                         const double *b, const XS &x, double *dst, bool dot, hipStream_t s) {
+    if (walk) {
+        const dim3 grid(static_cast<unsigned>(std::max<int32_t>(1, bw.blocks)));
+        if (dot)
+            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<XS, true>), grid, dim3(kBwBlock), 0, s, P->sp, L, bw,
+                      v.diag, v.coef, b, x, dst, P->part, P->state);
+        else
+            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<XS, false>), grid, dim3(kBwBlock), 0, s, P->sp, L, bw,
+                      v.diag, v.coef, b, x, dst, P->part, P->state);
+    } else {
+        if (dot)
+            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep<XS, true>), grid_for(L.n), dim3(kCellBlock), 0, s, P->sp, L,
+                      v.diag, v.coef, b, x, dst, P->part, P->state);
+        else
+            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep<XS, false>), grid_for(L.n), dim3(kCellBlock), 0, s, P->sp,
+                      L, v.diag, v.coef, b, x, dst, P->part, P->state);
+    }
+}
+
 // One cycle on level l for the right side b; the result ends in `out` when
 // given (level 0: w, with the w.r partials), else in one of the level's work
-// vectors, which is returned.
+// vectors, which is returned.  The first two sweeps are one launch, and the
+// first sweep after the coarse correction also adds it.
 static const double *amg_cycle(lf_problem *P, size_t l, const double *b, double *out, hipStream_t s) {
+    if (l > 0 && l == P->amg_tail) return amg_tail(P, l, b, s);
     const AmgView v = amg_view(P, l);
     const BandLayout<3> L = box_layout(v.nx, v.ny, v.nz);
-    const int32_t n = L.n;
     const bool coarsest = l == P->amg.size();
-    double *cur = nullptr;
     const int walk = P->amg_walk[l];
     const BoxWalk bw = P->amg_bw[l];
-    const dim3 wgrid(static_cast<unsigned>(std::max<int32_t>(1, bw.blocks)));
-    // the first sweep of a level starts from x = 0; level 0's last one (never
-    // its first: two or more sweeps per level) also forms the w.r partials.
-    // On a walked level the first two sweeps are one launch, the first sweep
-    // after the coarse correction also adds it (prolongation), and the other
-    // sweeps take the walk too.
-    const double *pending = nullptr;   // coarse result not yet added to cur
-    const AmgLevel *cl = coarsest ? nullptr : &P->amg[l];
-    auto sweep = [&](double *dst, bool last, bool can_pair) {
-        const bool dot = last && l == 0;
-        if (!cur && walk && can_pair) {
-            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<AmgFirstX, false>), wgrid, dim3(kBwBlock), 0, s, P->sp,
-                      L, bw, v.diag, v.coef, b, AmgFirstX{b, v.diag}, dst, P->part, P->state);
-            cur = dst;
-            return 2;
-        }
-        if (!cur) {
-            LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, k_amg_first, grid_for(n), dim3(kCellBlock), 0, s, n, b, v.diag, dst,
-                      P->state);
-        } else if (walk && pending) {
-            const AmgProlongX px{cur, pending, v.nx, v.ny, cl->nx, cl->ny, fast_div(static_cast<uint32_t>(v.nx)),
-                                 fast_div(static_cast<uint32_t>(v.ny))};
-            if (dot)
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<AmgProlongX, true>), wgrid, dim3(kBwBlock), 0, s,
-                          P->sp, L, bw, v.diag, v.coef, b, px, dst, P->part, P->state);
-            else
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<AmgProlongX, false>), wgrid, dim3(kBwBlock), 0, s,
-                          P->sp, L, bw, v.diag, v.coef, b, px, dst, P->part, P->state);
-        } else if (walk) {
-            if (dot)
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<MemX<double, 2>, true>), wgrid, dim3(kBwBlock), 0,
-                          s, P->sp, L, bw, v.diag, v.coef, b, MemX<double, 2>{cur}, dst, P->part, P->state);
-            else
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, (k_amg_sweep_box<MemX<double, 2>, false>), wgrid, dim3(kBwBlock), 0,
-                          s, P->sp, L, bw, v.diag, v.coef, b, MemX<double, 2>{cur}, dst, P->part, P->state);
-        } else {
-            if (pending)
-                LF_LAUNCH(P, LF_K_AMG_PROLONG, s, k_amg_prolong, grid_for(n), dim3(kCellBlock), 0, s, v.nx, v.ny, n,
-                          cl->nx, cl->ny, cur, pending, P->state);
-            if (dot)
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, k_amg_sweep<true>, grid_for(n), dim3(kCellBlock), 0, s, P->sp, L,
-                          v.diag, v.coef, b, cur, dst, P->part, P->state);
-            else
-                LF_LAUNCH(P, LF_K_AMG_SMOOTH, s, k_amg_sweep<false>, grid_for(n), dim3(kCellBlock), 0, s, P->sp, L,
-                          v.diag, v.coef, b, cur, dst, P->part, P->state);
-        }
-        pending = nullptr;
-        cur = dst;
-        return 1;
-    };
-    auto other = [&]() { return cur == v.ta ? v.tb : v.ta; };
+    typedef MemX<double, 2> X;
+    launch_sweep(P, v, L, walk, bw, b, AmgFirstX{b, v.diag}, v.ta, false, s);
     if (coarsest) {
-        for (int k = 0; k < kAmgNuC;) {
-            // the last sweep writes `out`: a fused first pair must end before it
-            const bool last = k == kAmgNuC - 1;
-            k += sweep(last && out ? out : other(), last, k + 2 < kAmgNuC);
-        }
-        return cur;
+        launch_sweep(P, v, L, walk, bw, b, X{v.ta}, v.tb, false, s);
+        double *dst = out ? out : v.ta;
+        launch_sweep(P, v, L, walk, bw, b, X{v.tb}, dst, l == 0, s);
+        return dst;
     }
-    for (int k = 0; k < kAmgNu;) k += sweep(other(), false, k + 2 <= kAmgNu);
     AmgLevel &c = P->amg[l];
     if (walk == 2)
-        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict_box, wgrid, dim3(kBwBlock), 0, s, L, bw, v.diag, v.coef, b,
-                  cur, c.b, P->state);
+        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict_box, dim3(static_cast<unsigned>(bw.blocks)), dim3(kBwBlock),
+                  0, s, L, bw, v.diag, v.coef, b, v.ta, c.b, P->state);
     else
-        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict, grid_for(c.n), dim3(kCellBlock), 0, s, L, v.nx, v.ny,
-                  v.nz, v.diag, v.coef, b, cur, c.nx, c.ny, c.n, c.b, P->state);
-    pending = amg_cycle(P, l + 1, c.b, nullptr, s);
-    for (int k = 0; k < kAmgNu; ++k) {
-        const bool last = k == kAmgNu - 1;
-        sweep(last && out ? out : other(), last, false);
-    }
-    return cur;
+        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict, grid_for(8 * static_cast<int64_t>(c.n)), dim3(kCellBlock), 0, s, L, v.nx, v.ny,
+                  v.nz, v.diag, v.coef, b, v.ta, c.nx, c.ny, c.n, c.b, P->state);
+    const double *xc = amg_cycle(P, l + 1, c.b, nullptr, s);
+    const AmgProlongX px{v.ta, xc, v.nx, v.ny, c.nx, c.ny, fast_div(static_cast<uint32_t>(v.nx)),
+                         fast_div(static_cast<uint32_t>(v.ny))};
+    launch_sweep(P, v, L, walk, bw, b, px, v.tb, false, s);
+    double *dst = out ? out : v.ta;
+    launch_sweep(P, v, L, walk, bw, b, X{v.tb}, dst, l == 0, s);
+    return dst;
 }
 
 void launch_amg_cycle(lf_problem *P, hipStream_t s) { amg_cycle(P, 0, P->r, P->w, s); }

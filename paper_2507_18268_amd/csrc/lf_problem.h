@@ -195,6 +195,7 @@ struct lf_problem {
     // sweeps walk, 2 the restriction too (all sides even)
     std::vector<lf::BoxWalk> amg_bw;
     std::vector<int8_t> amg_walk;
+    size_t amg_tail = 0;   // first level of the cycle's part in one workgroup (0: none)
     double *upper = nullptr;                   // [F] face order (test hook copy)
     double *coef = nullptr;                    // [n_entries] row layout or [n_bands N] bands
     double *int_coeff = nullptr, *bou_coeff = nullptr;
