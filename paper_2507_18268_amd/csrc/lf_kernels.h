@@ -1350,13 +1350,6 @@ __device__ __forceinline__ void row_amul_sum(const RBLayout &, int32_t, const do
     }
 }
 
-__device__ __forceinline__ void store_coef32(const RBLayout &L, int32_t c, const double *__restrict__,
-                                             const RowCoefs<RBLayout> &rc, float *__restrict__ coef32) {
-    if (c >= L.f.nr) return;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) coef32[static_cast<int64_t>(j) * L.f.nr + c] = static_cast<float>(rc.a[j]);
-}
-
 __device__ __forceinline__ void row_amul_sum(const SellLayout &L, int32_t c, const double *__restrict__ coef,
                                              const RowCoefs<SellLayout> &, const double *__restrict__ x,
                                              double &ax, double &sa) {
@@ -1380,21 +1373,6 @@ __device__ __forceinline__ void row_amul_sum(const BandLayout<K> &L, int32_t c, 
         ax += rc.a[j] * xv[j];
         sa += rc.a[j];
     }
-}
-
-// FP32 copy of the row's stored coefficients (precision form)
-__device__ __forceinline__ void store_coef32(const SellLayout &L, int32_t c, const double *__restrict__ coef,
-                                             const RowCoefs<SellLayout> &, float *__restrict__ coef32) {
-    int32_t idx = row_base(L.mr, c);
-    const int32_t len = L.mr.rlen[c];
-    for (int32_t j = 0; j < len; ++j, idx += kSlice) coef32[idx] = static_cast<float>(coef[idx]);
-}
-
-template <int K>
-__device__ __forceinline__ void store_coef32(const BandLayout<K> &L, int32_t c, const double *__restrict__,
-                                             const RowCoefs<BandLayout<K>> &rc, float *__restrict__ coef32) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) coef32[static_cast<int64_t>(k) * L.n + c] = static_cast<float>(rc.a[K + k]);
 }
 
 }  // namespace lf

@@ -1112,43 +1112,6 @@ k_dic_update_forward_rb(SolverParams sp, RBLayout L, const double *__restrict__ 
     write_partials<1>(part, sp.grid, slots, acc);
 }
 
-// backward sweep on red rows; every row contributes its w.r partial
-__global__ void __launch_bounds__(kCellBlock)
-k_dic_backward_rb(SolverParams sp, RBLayout L, const double *__restrict__ coef, const double *__restrict__ rD,
-                  const double *__restrict__ r, double *__restrict__ w, double *__restrict__ part,
-                  const PcgState *__restrict__ st) {
-    if (st->done) return;
-    const int32_t c = static_cast<int32_t>(blockIdx.x) * kCellBlock + static_cast<int32_t>(threadIdx.x);
-    double acc[1] = {0.0};
-    if (c < sp.n) {
-        const double rc = r[c];
-        double wc;
-        if (c < sp.n_red) {
-            const double rd = rD[c];
-            wc = rd * rc;
-            int64_t slot[6];
-            int32_t col[6];
-            bool ok[6];
-            rb_row(L.f, c, slot, col, ok);
-            double a[6], wo[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) {
-                a[j] = coef[slot[j]];
-                wo[j] = w[col[j]];
-            }
-#pragma unroll
-            for (int j = 5; j >= 0; --j)
-                if (ok[j]) wc -= rd * a[j] * wo[j];
-            w[c] = wc;
-        } else {
-            wc = w[c];
-        }
-        acc[0] = wc * rc;
-    }
-    const int slots[1] = {kPartWr};
-    write_partials<1>(part, sp.grid, slots, acc);
-}
-
 // q = A p on the two-colour band layout, one thread per half-index u taking
 // the red row u and the black row nr + u (x-neighbours on the box, so the
 // coefficients a black row gathers from its red neighbours' slots are read
