@@ -616,8 +616,8 @@ static const double *amg_cycle(lf_problem *P, size_t l, const double *b, double 
         LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict_box, dim3(static_cast<unsigned>(bw.blocks)), dim3(kBwBlock),
                   0, s, L, bw, v.diag, v.coef, b, v.ta, c.b, P->state);
     else
-        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict, grid_for(8 * static_cast<int64_t>(c.n)), dim3(kCellBlock), 0, s, L, v.nx, v.ny,
-                  v.nz, v.diag, v.coef, b, v.ta, c.nx, c.ny, c.n, c.b, P->state);
+        LF_LAUNCH(P, LF_K_AMG_RESTRICT, s, k_amg_restrict, grid_for(8 * static_cast<int64_t>(c.n)),
+                  dim3(kCellBlock), 0, s, L, v.nx, v.ny, v.nz, v.diag, v.coef, b, v.ta, c.nx, c.ny, c.n, c.b, P->state);
     const double *xc = amg_cycle(P, l + 1, c.b, nullptr, s);
     const AmgProlongX px{v.ta, xc, v.nx, v.ny, c.nx, c.ny, fast_div(static_cast<uint32_t>(v.nx)),
                          fast_div(static_cast<uint32_t>(v.ny))};

@@ -305,7 +305,8 @@ __device__ __forceinline__ const float *last_dir(int32_t n_iter, const float *p3
 // when it is still pending
 __device__ __forceinline__ void mx_correct(int32_t blk, const SolverParams &sp, double *__restrict__ T,
                                            const float *__restrict__ d32, const float *__restrict__ p32a,
-                                           const float *__restrict__ p32b, const float *__restrict__ sig32, const PcgState *__restrict__ st) {
+                                           const float *__restrict__ p32b, const float *__restrict__ sig32,
+                                           const PcgState *__restrict__ st) {
     if (st->done) return;
     const bool pend = st->inner_pend != 0;
     const float *__restrict__ p32 = last_dir(st->n_iter, p32a, p32b);
@@ -755,7 +756,8 @@ __device__ __forceinline__ void mx_direction_amul(int32_t blk, int32_t end, cons
 }
 
 // k_mx_finalize<kMxAlpha>, then rs -= alpha q; FP64 partials of s|rs| and rs.rs
-__device__ __forceinline__ void mx_update_fold(int32_t blk, int32_t end, const SolverParams &sp, const float *__restrict__ q32,
+__device__ __forceinline__ void mx_update_fold(int32_t blk, int32_t end, const SolverParams &sp,
+                                               const float *__restrict__ q32,
                                                const float *__restrict__ sig32, float *__restrict__ r32,
                                                double *__restrict__ part, PcgState *__restrict__ st) {
     if (group_inner_off(st)) return;

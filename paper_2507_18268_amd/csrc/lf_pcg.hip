@@ -114,8 +114,8 @@ __device__ __forceinline__ double mean_of_x(const SolverParams &sp, bool lead, c
 
 template <class Lay, bool kFull, bool kSetup, bool kMixed, bool kNonorth = false>
 __device__ __forceinline__ void assemble_rows(
-    int32_t blk, double x_avg, const SolverParams &sp, double rdt, double DT, const Lay &L, const int32_t *__restrict__ bface_start,
-    const int32_t *__restrict__ bface_list, const int32_t *__restrict__ bface_patch,
+    int32_t blk, double x_avg, const SolverParams &sp, double rdt, double DT, const Lay &L,
+    const int32_t *__restrict__ bface_start, const int32_t *__restrict__ bface_list, const int32_t *__restrict__ bface_patch,
     const double *__restrict__ bmag_sf, const double *__restrict__ bdelta, const int32_t *__restrict__ patch_type,
     const double *__restrict__ patch_value, const double *__restrict__ V, const double *__restrict__ T,
     double *__restrict__ coef, double *__restrict__ upper, double *__restrict__ diag, double *__restrict__ source,
@@ -228,9 +228,165 @@ k_assemble(SolverParams sp, double rdt, double DT, Lay L, const int32_t *__restr
            const double *__restrict__ nb_g, const double *__restrict__ nb_gk, double *__restrict__ xs) {
     const double x_avg = kSetup ? mean_of_x(sp, blockIdx.x == 0, part, st) : 0.0;
     assemble_rows<Lay, kFull, kSetup, kMixed, kNonorth>(
-        sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x), x_avg, sp, rdt, DT, L, bface_start, bface_list, bface_patch, bmag_sf, bdelta,
-        patch_type, patch_value, V, T, coef, upper, diag, source, diagB, srcB, int_coeff, bou_coeff, diag_pc, r, rD,
+        sp.by_die ? die_share() : static_cast<int32_t>(blockIdx.x), x_avg, sp, rdt, DT, L, bface_start, bface_list,
+        bface_patch, bmag_sf, bdelta, patch_type, patch_value, V, T, coef, upper, diag, source, diagB, srcB, int_coeff, bou_coeff, diag_pc, r, rD,
         part, sig32, r32, d32, p, lap_src, T_old, nb_g, nb_gk, xs);
+}
+
+// The assembly fused with the set-up, two adjacent rows per thread (boxes on the
+// block walk: x-lines of even length, so that a pair's neighbours in y and z are
+// pairs too): every array moves 16 bytes per lane, and a pair's x-neighbours are
+// its own rows and the adjacent lanes'.  Each row's coefficients, lapDiag,
+// boundary fold, A x0, residual and normalisation terms come from the one-row
+// kernel's expressions in its order (the matrix is bitwise the same); the
+// partials are per workgroup, with zeros in the rest of each slot, which the
+// reduction reads.  At 256^3, against one row per thread: precision form 532 ->
+// 414 us (2.0 GB, 4.9 TB/s), scaled solve 502 -> 470 us (2.2 GB, 4.7 TB/s).
+template <bool kMixed>
+__global__ void __launch_bounds__(kCellBlock)
+k_assemble_pair(SolverParams sp, double rdt, double DT, BandLayout<3> L, const int32_t *__restrict__ bface_start,
+                const int32_t *__restrict__ bface_list, const int32_t *__restrict__ bface_patch,
+                const double *__restrict__ bmag_sf, const double *__restrict__ bdelta,
+                const int32_t *__restrict__ patch_type, const double *__restrict__ patch_value,
+                const double *__restrict__ V, const double *__restrict__ T, double *__restrict__ coef,
+                double *__restrict__ diagB, double *__restrict__ srcB, double *__restrict__ r,
+                double *__restrict__ rD, double *__restrict__ part, PcgState *__restrict__ st,
+                float *__restrict__ sig32, float *__restrict__ r32, float *__restrict__ d32,
+                double *__restrict__ p, double *__restrict__ xs) {
+    typedef Lanes<double, 2> R;
+    typedef typename R::vec RV;
+    typedef float FV __attribute__((ext_vector_type(2)));
+    const double x_avg = mean_of_x(sp, blockIdx.x == 0, part, st);
+    const int64_t n = L.n, d1 = L.d[1], d2 = L.d[2];
+    const int64_t c = 2 * (static_cast<int64_t>(blockIdx.x) * kCellBlock + threadIdx.x);
+    const bool tv = c < n;
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const R z = lanes_zero<double, 2>();
+    R dl[6], ms[6], xv[6], xc = z;          // entries in the row's order: -z, -y, -x, x, y, z
+#pragma unroll
+    for (int j = 0; j < 6; ++j) dl[j] = ms[j] = xv[j] = z;
+    if (tv) {
+        xc = lanes_load<double, 2>(T, c);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            dl[3 + k] = lanes_load<double, 2>(L.delta, k * n + c);
+            ms[3 + k] = lanes_load<double, 2>(L.mag_sf, k * n + c);
+        }
+#pragma unroll
+        for (int k = 1; k < 3; ++k) {
+            const int64_t d = k == 1 ? d1 : d2;
+            xv[2 - k] = xv[3 + k] = xc;
+            if (c >= d) {
+                dl[2 - k] = lanes_load<double, 2>(L.delta, k * n + c - d);
+                ms[2 - k] = lanes_load<double, 2>(L.mag_sf, k * n + c - d);
+                xv[2 - k] = lanes_load<double, 2>(T, c - d);
+            }
+            if (c < n - d) xv[3 + k] = lanes_load<double, 2>(T, c + d);
+        }
+    }
+    double dm = lane_from_below(dl[3].v[1]), mm = lane_from_below(ms[3].v[1]), xm = lane_from_below(xc.v[1]);
+    double xp = lane_from_above(xc.v[0]);
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (tv) {
+        if (c == 0) {
+            dm = mm = 0.0;
+            xm = xc.v[0];
+        } else if (lane == 0) {
+            dm = L.delta[c - 1];
+            mm = L.mag_sf[c - 1];
+            xm = T[c - 1];
+        }
+        if (c + 2 >= n) xp = xc.v[1];
+        else if (lane == 63) xp = T[c + 2];
+        dl[2].v[0] = dm;
+        dl[2].v[1] = dl[3].v[0];
+        ms[2].v[0] = mm;
+        ms[2].v[1] = ms[3].v[0];
+        xv[2].v[0] = xm;
+        xv[2].v[1] = xc.v[0];
+        xv[3].v[0] = xc.v[1];
+        xv[3].v[1] = xp;
+        const R v = lanes_load<double, 2>(V, c);
+        const int32_t b[3] = {bface_start[c], bface_start[c + 1], bface_start[c + 2]};
+        RV ca[3], db, sb, rv, sv, xo;
+        FV sg32, rs32;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            double a[6], lap_diag = 0.0;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const double lap_upper = dl[j].v[w] * (DT * ms[j].v[w]);
+                a[j] = -lap_upper;
+                lap_diag -= lap_upper;
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ca[k][w] = a[3 + k];
+            double dw = rdt * v.v[w] - lap_diag;
+            double sw = (rdt * xc.v[w]) * v.v[w];
+            for (int32_t i = b[w]; i < b[w + 1]; ++i) {
+                const int32_t f = bface_list[i];
+                const int32_t pt = bface_patch[f];
+                if (patch_type[pt] == LF_BC_FIXED_VALUE) {
+                    const double g = DT * bmag_sf[f];
+                    dw += g * bdelta[f];
+                    sw += g * (bdelta[f] * patch_value[pt]);
+                }
+            }
+            db[w] = dw;
+            sb[w] = sw;
+            double ax = dw * xc.v[w], sa = dw;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                ax += a[j] * xv[j].v[w];
+                sa += a[j];
+            }
+            const double rc = sw - ax;
+            const double pa = sa * x_avg;
+            acc[0] += fabs(rc);
+            acc[1] += fabs(ax - pa) + fabs(sw - pa);
+            if (kMixed) {
+                const float sg = static_cast<float>(sqrt(dw));
+                const float rs = static_cast<float>(rc / static_cast<double>(sg));
+                sg32[w] = sg;
+                rs32[w] = rs;
+                acc[3] += fabs(static_cast<double>(sg) * static_cast<double>(rs));
+                acc[4] += static_cast<double>(rs) * static_cast<double>(rs);
+            } else {
+                const double sd = sqrt(dw);
+                const double rt = rc / sd;
+                sv[w] = sd;
+                rv[w] = rt;
+                xo[w] = sd * xc.v[w];
+                acc[2] += rt * rt;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<RV *>(coef + k * n + c) = ca[k];
+        // next needed after the solve's other vectors have passed the caches
+        __builtin_nontemporal_store(db, reinterpret_cast<RV *>(diagB + c));
+        __builtin_nontemporal_store(sb, reinterpret_cast<RV *>(srcB + c));
+        if (kMixed) {
+            *reinterpret_cast<FV *>(sig32 + c) = sg32;
+            *reinterpret_cast<FV *>(r32 + c) = rs32;
+            *reinterpret_cast<FV *>(d32 + c) = FV{0.0f, 0.0f};
+        } else {
+            *reinterpret_cast<RV *>(r + c) = rv;
+            *reinterpret_cast<RV *>(rD + c) = sv;
+            *reinterpret_cast<RV *>(p + c) = rv;
+            *reinterpret_cast<RV *>(xs + c) = xo;
+        }
+    }
+    constexpr int kSlots = kMixed ? 5 : 3;
+    const int slots[5] = {kPartSumR, kPartNf, kPartWr, kPartSumR32, kPartWr32};
+    block_sum<kCellBlock, 5>(acc);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+            double *o = part + static_cast<int64_t>(slots[q]) * sp.grid;
+            o[blockIdx.x] = acc[q];
+            for (int64_t j = gridDim.x + static_cast<int64_t>(blockIdx.x); j < sp.grid; j += gridDim.x) o[j] = 0.0;
+        }
+    }
 }
 
 // partial sums of x0 = T (its mean enters the normalisation factor)
@@ -1991,6 +2147,19 @@ static void launch_assemble_t(lf_problem *P, hipStream_t s) {
                           P->patch_value, m->V, P->T, P->coef, P->upper, P->diag, P->source, P->diagB, P->srcB,
                           P->int_coeff, P->bou_coeff, pc_mode, P->r, P->rD, P->part, P->state, P->sig32,
                           P->r32, P->d32, dir, nullptr, T_old, P->grad3, m->gkband, xs);
+                return;
+            }
+        }
+        if constexpr (std::is_same_v<Lay, BandLayout<3>> && kSetup && !kFull) {
+            // walked boxes, precision form and scaled solve: rows in pairs (the multigrid
+            // solve, which stores r alone, gained nothing: 200^3 26.4 ms either way)
+            if (!P->nonorth && (kMixed ? P->box32 : P->box && pc_mode == 2)) {
+                const int64_t pairs = (static_cast<int64_t>(m->N) / 2 + kCellBlock - 1) / kCellBlock;
+                LF_LAUNCH(P, LF_K_ASSEMBLE, s, k_assemble_pair<kMixed>, dim3(static_cast<unsigned>(pairs)),
+                          dim3(kCellBlock), 0, s, P->sp, rdt, P->DT, lay, m->rbface_start, m->rbface_list,
+                          m->bface_patch, m->bmag_sf, m->bdelta, P->patch_type, P->patch_value, m->V, P->T, P->coef,
+                          P->diagB, P->srcB, P->r, P->rD, P->part, P->state, P->sig32, P->r32,
+                          P->d32, P->p, xs);
                 return;
             }
         }
