@@ -549,9 +549,11 @@ lf_status lf_group_poll(lf_group *group, lf_problem **finished, int32_t max_fini
 #define LF_K_MIXED_PREP 14      /* mixed: FP32 coefficients of the scaled matrix
                                    (once per step) */
 #define LF_K_FINALIZE 15        /* one-workgroup reductions and scalar decisions */
-#define LF_K_AMG_SMOOTH 16      /* multigrid: Jacobi sweeps (all levels) */
+#define LF_K_AMG_SMOOTH 16      /* multigrid: Jacobi sweeps (all levels; the last levels'
+                                   part of the cycle in one launch) */
 #define LF_K_AMG_RESTRICT 17    /* multigrid: residual summed over the aggregates */
-#define LF_K_AMG_PROLONG 18     /* multigrid: coarse correction added back */
+#define LF_K_AMG_PROLONG 18     /* multigrid: coarse correction added back (part of the
+                                   sweep after it: no launches of its own) */
 #define LF_K_AMG_GALERKIN 19    /* multigrid: coarse matrices (once per step) */
 #define LF_K_GRAD 20            /* non-orthogonal meshes: the gradient of T before
                                    each assembly (solver order) */
