@@ -2517,7 +2517,8 @@ static lf_status fp64_block(lf_problem *P, SolveCtx &c) {
     c.launched += c.k;
     // the commit follows in the same block, so that the host waits once per
     // block and not again after it (the timing runs launch it when it is due)
-    if (!P->prof_on) launch_commit(P, s, P->d_hstate);
+    c.committed = !P->prof_on;
+    if (c.committed) launch_commit(P, s, P->d_hstate);
     else launch_publish(P, s);
     LF_HIP(hipGetLastError());
     LF_HIP(hipEventRecord(P->ev[2], s));
@@ -2531,7 +2532,6 @@ lf_status fp64_start(lf_problem *P, SolveCtx &c) {
     c.fixed_k = P->prof_on ? 1 : P->opts.iters_per_check;
     c.k = c.fixed_k > 0 ? c.fixed_k : P->last_iters > 0 ? P->last_iters : 8;
     c.launched = 0;
-    c.stage = 0;
     return fp64_block(P, c);
 }
 
@@ -2540,12 +2540,13 @@ lf_status fp64_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_stat
     prof_flush(P);
     *finished = false;
     const PcgState &h = *P->h_state;
-    if (h.done && P->prof_on && c.stage == 0) {
+    // by what was enqueued: the timers may have been switched since
+    if (h.done && !c.committed) {
         prof_lead(P, s);
         launch_commit(P, s, nullptr);
         LF_HIP(hipGetLastError());
         LF_HIP(hipEventRecord(P->ev[2], s));
-        c.stage = 1;
+        c.committed = true;
         return LF_OK;
     }
     if (h.done) {

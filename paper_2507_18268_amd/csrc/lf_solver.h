@@ -124,8 +124,9 @@ struct SolveCtx {
     int32_t fixed_k = 0;   // iterations per block when fixed (>0), else adaptive
     int32_t k = 0;         // iterations of the next block
     int32_t launched = 0;  // iterations enqueued so far
-    int32_t stage = 0;     // FP64: 0 iterating, 1 committing; mixed: 1 awaiting the
-                           // outer check of a pass before starting another
+    bool committed = false;// FP64: the commit was enqueued behind the last block
+    int32_t stage = 0;     // mixed: 1 awaiting the outer check of a pass before
+                           // starting another
 };
 lf_status fp64_start(lf_problem *P, SolveCtx &c);
 lf_status fp64_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_stats *out);
