@@ -61,14 +61,22 @@ __device__ __forceinline__ void bsum2(double &a0, double &a1) {
     a1 = a[1];
 }
 
+// Up to this many rows (kNear) a row's byte offset in any array fits the 32 bits
+// of an access's offset register, the rows that a last group reaches past the
+// end (at most 2^14) among them.  Addresses good for any row would cost 1-2%
+// with 512 threads and 9-18% with 1024, so larger problems have a form of their
+// own, one row after the other.
+constexpr int32_t kNearRows = (1 << 28) - (1 << 14);
+
 // fn(rows) for the thread's groups in order.  A group is an inner one if all its
 // rows are at least `halo` rows from both ends.
-template <int BS, int G, class Fn>
+template <int BS, int G, bool kNear, class Fn>
 __device__ __forceinline__ void each_group(int32_t n, int32_t halo, Fn &&fn) {
+    static_assert(G * BS <= 1 << 14, "kNearRows leaves room for one group");
     for (int32_t i = 0; i < n; i += G * BS) {
         const uint32_t c0 = static_cast<uint32_t>(i) + threadIdx.x;
-        __builtin_assume(c0 < (1u << 28));
-        if (i >= halo && i + G * BS + halo <= n)
+        if (kNear) __builtin_assume(c0 < (1u << 28));
+        if (i >= halo && i + G * BS <= n - halo)
             fn(RowGroup<BS, G, true>{c0, n - 1});
         else
             fn(RowGroup<BS, G, false>{c0, n - 1});
@@ -112,14 +120,14 @@ __device__ __forceinline__ void group_assemble(const BandLayout<3> &L, const Row
         for (int j = 0; j < 3; ++j) {
             const int k = 2 - j;
             if constexpr (kIn) {
-                dl[u][j] = g.at(L.delta, u, k * L.n - L.d[k]);
+                dl[u][j] = g.at(L.delta + static_cast<int64_t>(k) * L.n, u, -L.d[k]);
             } else {
                 const int32_t c = g.row(u);
-                dl[u][j] = L.delta[k * L.n + (c >= L.d[k] ? c - L.d[k] : L.n - 1)];
+                dl[u][j] = L.delta[static_cast<int64_t>(k) * L.n + (c >= L.d[k] ? c - L.d[k] : L.n - 1)];
             }
         }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) dl[u][3 + k] = g.at(L.delta, u, k * L.n);
+        for (int k = 0; k < 3; ++k) dl[u][3 + k] = g.at(L.delta + static_cast<int64_t>(k) * L.n, u);
     }
 #pragma unroll
     for (int u = 0; u < G; ++u) {
@@ -131,7 +139,7 @@ __device__ __forceinline__ void group_assemble(const BandLayout<3> &L, const Row
             lap[u] -= up;
         }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) g.set(coef + k * L.n, u, a[u][3 + k]);
+        for (int k = 0; k < 3; ++k) g.set(coef + static_cast<int64_t>(k) * L.n, u, a[u][3 + k]);
     }
 }
 
@@ -147,7 +155,7 @@ __device__ __forceinline__ void group_scale(const BandLayout<3> &L, const RowGro
         tc[u] = g.at(t32, u);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            a[u][k] = g.at(coef, u, k * L.n);
+            a[u][k] = g.at(coef + static_cast<int64_t>(k) * L.n, u);
             if constexpr (kIn) {
                 tn[u][k] = g.at(t32, u, L.d[k]);
             } else {
@@ -160,7 +168,7 @@ __device__ __forceinline__ void group_scale(const BandLayout<3> &L, const RowGro
     for (int u = 0; u < G; ++u)
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            g.set(coef32 + k * L.n, u,
+            g.set(coef32 + static_cast<int64_t>(k) * L.n, u,
                   static_cast<float>(a[u][k] * (static_cast<double>(tc[u]) * static_cast<double>(tn[u][k]))));
 }
 
@@ -195,7 +203,7 @@ __device__ __forceinline__ void group_scale(const SellLayout &L, const RowGroup<
 //
 // The task's arrays are distinct allocations: taking them into __restrict__
 // locals lets the compiler overlap the loads of several rows of a loop.
-template <int BS, int kLds, class Lay>
+template <int BS, int kLds, bool kNear, class Lay>
 __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps,
                                            lf_solve_stats *__restrict__ stats, float *lds) {
     const int32_t n = tk.n;
@@ -228,14 +236,14 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
     // many rows as the registers (131072 / BS per thread) hold loads for, in
     // the FP32 vector updates (kG), the FP32 product (kGP), the FP64 product
     // (kG64) and the assembly (kGA).
-    constexpr int kG = BS == 1024 ? 8 : 16, kGP = BS == 1024 ? 4 : 8;
-    constexpr int kG64 = BS == 1024 ? 2 : 4, kGA = BS == 1024 ? 1 : 4;
+    constexpr int kG = !kNear ? 1 : BS == 1024 ? 8 : 16, kGP = !kNear ? 1 : BS == 1024 ? 4 : 8;
+    constexpr int kG64 = !kNear ? 1 : BS == 1024 ? 2 : 4, kGA = !kNear || BS == 1024 ? 1 : 4;
     constexpr bool kBand = !std::is_same_v<Lay, SellLayout>;
     int32_t halo = n;                 // rows between a row and its farthest neighbour (rows: unknown)
     if constexpr (kBand) halo = L.d[2];
     // sum of x0 = T; the later steps' is taken with the last residual
     double sx = 0.0;
-    each_group<BS, kG>(n, 0, [&](const auto &g) {
+    each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
         double x[kG];
 #pragma unroll
         for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
@@ -286,7 +294,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             a_nf += fabs(ax - pa) + fabs(sb - pa);
         };
         if constexpr (kBand) {
-            each_group<BS, kGA>(n, halo, [&](const auto &g) {
+            each_group<BS, kGA, kNear>(n, halo, [&](const auto &g) {
                 double a[kGA][6], xv[kGA][6], lap[kGA], v[kGA], xc[kGA], bd[kGA], bs[kGA];
                 int32_t b0[kGA], b1[kGA];
 #pragma unroll
@@ -349,7 +357,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             s_r = a[2];
             s_wr = a[3];
         }
-        each_group<BS, kG64>(n, halo, [&](const auto &g) { group_scale(L, g, t32, coef, coef32); });
+        each_group<BS, kG64, kNear>(n, halo, [&](const auto &g) { group_scale(L, g, t32, coef, coef32); });
         const double nf = a_nf + 1e-20;
         const double res0 = a_r / nf;
         double res = res0;
@@ -368,7 +376,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             while (!inner_done) {
                 if (inner_iter > 0) {          // p = rs in the first iteration
                     const float fb = static_cast<float>(beta);
-                    each_group<BS, kG>(n, 0, [&](const auto &g) {
+                    each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
                         float rs[kG], pc[kG];
 #pragma unroll
                         for (int u = 0; u < kG; ++u) {
@@ -381,7 +389,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
                     __syncthreads();
                 }
                 double s_pq = 0.0;
-                each_group<BS, kGP>(n, halo, [&](const auto &g) {
+                each_group<BS, kGP, kNear>(n, halo, [&](const auto &g) {
                     float pc[kGP], qc[kGP];
 #pragma unroll
                     for (int u = 0; u < kGP; ++u) pc[u] = g.at(p, u);
@@ -399,7 +407,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
                 const double alpha = wArA / pq;
                 const float fa = static_cast<float>(alpha);
                 double u_r = 0.0, u_wr = 0.0;
-                each_group<BS, kG>(n, 0, [&](const auto &g) {
+                each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
                     float sc[kG], pc[kG], rs[kG], q[kG], y[kG];
 #pragma unroll
                     for (int u = 0; u < kG; ++u) {
@@ -435,7 +443,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             }
             if (nonfinite) break;
             // T += d, then the FP64 true residual (and the sum of T)
-            each_group<BS, kG>(n, 0, [&](const auto &g) {
+            each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
                 double x[kG];
                 float tc[kG], y[kG];
 #pragma unroll
@@ -451,7 +459,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             __syncthreads();
             double o_r = 0.0, o_x = 0.0;
             s_r = s_wr = 0.0;
-            each_group<BS, kG64>(n, halo, [&](const auto &g) {
+            each_group<BS, kG64, kNear>(n, halo, [&](const auto &g) {
                 double xc[kG64], ax[kG64], b[kG64], y[kG64];
                 float sc[kG64], tc[kG64];
 #pragma unroll
@@ -492,7 +500,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
         if (tk.snap) {
             double *__restrict__ out = as_global(tk.snap) + static_cast<int64_t>(step) * n;
             const int32_t *__restrict__ ip = as_global(tk.iperm);
-            each_group<BS, kG>(n, 0, [&](const auto &g) {
+            each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
                 double x[kG];
 #pragma unroll
                 for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
@@ -534,7 +542,10 @@ __host__ __device__ inline int lds_vectors(int32_t n) {
     return n > kRows ? 0 : kRows / n < 4 ? kRows / n : 4;
 }
 
-template <int BS>
+// kNear: no task has more than kNearRows rows; else all run in the other form
+// (bitwise the same results; a kernel of its own, since beside it in one kernel
+// the near forms ran 2% slower)
+template <int BS, bool kNear>
 __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ tasks, int32_t n_tasks,
                                              int32_t *__restrict__ counter, int32_t n_steps,
                                              lf_solve_stats *__restrict__ stats) {
@@ -555,19 +566,23 @@ __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ task
             for (int k = 0; k < 3; ++k) L.d[k] = tk.band_d[k];
             L.mag_sf = as_global(tk.band_mag_sf);
             L.delta = as_global(tk.band_delta);
-            switch (lds_vectors(tk.n)) {
-                case 0: solve_task<BS, 0>(tk, L, n_steps, st, nullptr); break;
-                case 1: solve_task<BS, 1>(tk, L, n_steps, st, lds); break;
-                case 2: solve_task<BS, 2>(tk, L, n_steps, st, lds); break;
-                case 3: solve_task<BS, 3>(tk, L, n_steps, st, lds); break;
-                default: solve_task<BS, 4>(tk, L, n_steps, st, lds); break;
+            if constexpr (!kNear) {
+                solve_task<BS, 0, false>(tk, L, n_steps, st, nullptr);
+            } else {
+                switch (lds_vectors(tk.n)) {
+                    case 0: solve_task<BS, 0, true>(tk, L, n_steps, st, nullptr); break;
+                    case 1: solve_task<BS, 1, true>(tk, L, n_steps, st, lds); break;
+                    case 2: solve_task<BS, 2, true>(tk, L, n_steps, st, lds); break;
+                    case 3: solve_task<BS, 3, true>(tk, L, n_steps, st, lds); break;
+                    default: solve_task<BS, 4, true>(tk, L, n_steps, st, lds); break;
+                }
             }
         } else {
             const SellLayout L{MeshRows{as_global(tk.soff), as_global(tk.scol), as_global(tk.sface),
                                         as_global(tk.rlen)},
                                as_global(tk.mag_sf), as_global(tk.delta), as_global(tk.emag_sf),
                                as_global(tk.edelta)};
-            solve_task<BS, 0>(tk, L, n_steps, st, nullptr);
+            solve_task<BS, 0, kNear>(tk, L, n_steps, st, nullptr);
         }
     }
 }
@@ -595,13 +610,15 @@ struct lf_batch {
 // the kernel with the LDS of the launch's largest need (above 64 KiB it has to
 // be allowed first)
 template <int BS>
-static lf_status launch_batch(int32_t lds_rows, int32_t grid, int32_t n, int32_t n_steps, lf_batch *b, hipStream_t s) {
-    const int lds = static_cast<int>(sizeof(float)) * lds_rows;
+static lf_status launch_batch(bool near, int32_t lds_rows, int32_t grid, int32_t n, int32_t n_steps, lf_batch *b,
+                              hipStream_t s) {
+    const int lds = near ? static_cast<int>(sizeof(float)) * lds_rows : 0;
+    auto kern = near ? k_batch<BS, true> : k_batch<BS, false>;
     if (lds > (48 << 10))
-        LF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<BS>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, 156 << 10));
-    hipLaunchKernelGGL(k_batch<BS>, dim3(static_cast<unsigned>(grid)), dim3(BS), static_cast<unsigned>(lds), s,
-                       b->d_tasks, n, b->d_counter, n_steps, b->d_stats);
+        LF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   156 << 10));
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(BS), static_cast<unsigned>(lds), s, b->d_tasks, n,
+                       b->d_counter, n_steps, b->d_stats);
     return LF_OK;
 }
 
@@ -692,6 +709,7 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         }
     }
     int32_t lds_rows = 0;     // the launch's LDS, in floats
+    bool near = true;
     for (int32_t i = 0; i < n; ++i) {
         const lf_problem *P = problems[i];
         if (!P) { set_error("problem %d is NULL", i); return LF_EINVAL; }
@@ -732,6 +750,7 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         t.n = m->N; t.max_iter = P->sp.max_iter; t.max_outer = P->sp.max_outer;
         t.n_bfaces = m->B;
         if (t.nb == 3) lds_rows = std::max(lds_rows, lds_vectors(t.n) * t.n);
+        near = near && t.n <= kNearRows;
     }
     for (int32_t i = 0; i < n; ++i) problems[i]->sumx_valid = false;     // the launch rewrites T
     hipStream_t s = b->stream;
@@ -740,9 +759,9 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
     hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, s, b->d_counter);
     LF_HIP(hipEventRecord(b->start, s));
     switch (block_threads) {
-        case 256: LF_TRY(launch_batch<256>(lds_rows, g, n, n_steps, b, s)); break;
-        case 512: LF_TRY(launch_batch<512>(lds_rows, g, n, n_steps, b, s)); break;
-        default: LF_TRY(launch_batch<1024>(lds_rows, g, n, n_steps, b, s)); break;
+        case 256: LF_TRY(launch_batch<256>(near, lds_rows, g, n, n_steps, b, s)); break;
+        case 512: LF_TRY(launch_batch<512>(near, lds_rows, g, n, n_steps, b, s)); break;
+        default: LF_TRY(launch_batch<1024>(near, lds_rows, g, n, n_steps, b, s)); break;
     }
     LF_HIP(hipGetLastError());
     LF_HIP(hipMemcpyAsync(b->h_stats, b->d_stats, sizeof(lf_solve_stats) * static_cast<size_t>(n) * n_steps,
