@@ -585,8 +585,10 @@ static lf_status begin_step(StepDriver &d) {
     d.pass = 0;
     std::memset(&d.acc, 0, sizeof(d.acc));
     // the corrector passes take their ddt source from T at the start of the step
-    if (corrector_passes(P) > 0)
+    if (corrector_passes(P) > 0) {
         launch_copy(P->mesh->N, P->T, P->T_old, P->stream);
+        LF_HIP(hipGetLastError());
+    }
     return begin_pass(d);
 }
 
