@@ -233,12 +233,13 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
         P->sp.grid_sum = update_blocks(m->N);
         P->sp.by_die = m->N <= kFoldDieRows ? 1 : 0;
     }
-    // the precision form without a walk: two launches per inner iteration
+    // the precision form without a walk: two launches per inner iteration on
+    // small and middling meshes
     if (opts.precision == LF_PREC_MIXED && !P->walk) {
-        P->sp.mx_rows = m->N <= kMxOneRow ? 1 : (m->N <= kMxFoldStartRows ? kMxRows : kMxManyRows);
-        const int32_t tile = kCellBlock * P->sp.mx_rows;
+        P->sp.mx_rows = mx_two_rows(m->N, P->banded);
+        const int32_t tile = kCellBlock * (P->sp.mx_rows > 0 ? P->sp.mx_rows : kMxRows);
         P->sp.grid_mx = P->sp.grid_mx_amul = m->N > 0 ? (m->N - 1) / tile + 1 : 1;
-        P->sp.mx_fold_start = m->N <= kMxFoldStartRows ? 1 : 0;
+        P->sp.mx_fold_start = P->sp.mx_rows > 0 && m->N <= kMxFoldStartRows ? 1 : 0;
         P->sp.grid_sum = m->N <= kMxFoldMeanRows ? P->sp.grid : 0;
     }
     // larger diagonal FP64 solves on the block walk iterate on the Jacobi-scaled

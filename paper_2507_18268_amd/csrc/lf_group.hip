@@ -96,7 +96,7 @@ lf_status check_member(const lf_group *g, const lf_problem *P) {
     if (P->opts.precision != LF_PREC_MIXED) { set_error("a group runs LF_PREC_MIXED problems"); return LF_EINVAL; }
     if (P->opts.precond != LF_PC_DIAGONAL) { set_error("a group runs the diagonal preconditioner"); return LF_EINVAL; }
     if (P->nonorth) { set_error("a group runs orthogonal meshes (no corrector loop)"); return LF_EINVAL; }
-    if (P->walk || P->box || P->rb || P->too_large || P->sp.mx_rows <= 0) {
+    if (P->walk || P->box || P->rb || P->too_large) {
         set_error("a group runs the one-row-per-thread products (lf_problem_amul_walk 0) of meshes that do not fill the GPU "
                   "by themselves");
         return LF_EINVAL;
@@ -236,6 +236,9 @@ lf_status launch_next(lf_group *g) {
     const auto inner_blocks = [](const GroupMember &m) { return static_cast<int64_t>(m.P->sp.grid_mx); };
     // those whose start of a pass the one-workgroup kernels decide
     const auto big = [](const GroupMember &m) { return !m.P->sp.mx_fold_start; };
+    // those with two launches per inner iteration; the others have five
+    const auto two = [](const GroupMember &m) { return m.P->sp.mx_rows > 0; };
+    const auto five = [](const GroupMember &m) { return m.P->sp.mx_rows == 0; };
     const auto select = [g](const std::vector<int32_t> &slots, auto &&which) {
         std::vector<int32_t> v;
         for (const int32_t s : slots)
@@ -248,8 +251,8 @@ lf_status launch_next(lf_group *g) {
                            launch_of(g, select(starts, [](const GroupMember &m) { return m.P->sp.grid_sum == 0; }), cells),
                            st);
         launch_group_scale(g->d_tab, gl, st);
-        launch_group_solve_start(g->d_tab, launch_of(g, starts, inner_blocks), launch_of(g, select(starts, big), cells),
-                                 st);
+        launch_group_solve_start(g->d_tab, launch_of(g, select(starts, two), inner_blocks),
+                                 launch_of(g, select(starts, big), cells), st);
         for (const int32_t s : starts) {
             GroupMember &m = g->members[s];
             m.start = false;
@@ -260,13 +263,16 @@ lf_status launch_next(lf_group *g) {
     }
     if (!turns.empty()) {
         const GroupLaunch gl = launch_of(g, turns, cells);
-        launch_group_turn(g->d_tab, gl, launch_of(g, turns, inner_blocks), launch_of(g, select(turns, big), cells), st);
+        launch_group_turn(g->d_tab, gl, launch_of(g, select(turns, two), inner_blocks),
+                          launch_of(g, select(turns, big), cells), st);
         for (const int32_t s : turns) g->members[s].turn = false;
     }
     GroupLaunch gi{};
     if (!inner.empty()) {
         gi = launch_of(g, inner, inner_blocks);
-        for (int32_t k = 0; k < g->iters; ++k) launch_group_iteration(g->d_tab, gi, st);
+        const GroupLaunch g2 = launch_of(g, select(inner, two), inner_blocks);
+        const GroupLaunch g5 = launch_of(g, select(inner, five), inner_blocks);
+        for (int32_t k = 0; k < g->iters; ++k) launch_group_iteration(g->d_tab, g2, g5, st);
         launch_group_gather(g->d_tab, gi, g->d_hstates, st);
     }
     LF_HIP(hipGetLastError());

@@ -234,8 +234,36 @@ k_mx_update4(SolverParams sp, const float *__restrict__ q32, const float *__rest
     write_partials_at<2>(part, sp.grid, blk, slots, acc);
 }
 
-// q = As p in FP32 (unit diagonal: p_c first, then the row's entries in order)
-// by the row walk (band layouts with two or more bands), FP64 partial sums of p.q:
+// q = As p in FP32 (unit diagonal: p_c first, then the row's entries in
+// order); FP64 partial sums of p.q
+template <class Lay>
+__device__ __forceinline__ void mx_amul_dot(int32_t blk, const SolverParams &sp, const Lay &L,
+                                            const float *__restrict__ coef32, const float *__restrict__ p32,
+                                            float *__restrict__ q32, double *__restrict__ part,
+                                            const PcgState *__restrict__ st) {
+    if (inner_off(st)) return;
+    double acc[1] = {0.0};
+#pragma unroll
+    for (int j = 0; j < kMxRows; ++j) {
+        const int32_t c = cell_row_at<kMxRows>(blk, j);
+        if (c >= sp.n) continue;
+        const float pc = p32[c];
+        const float qc = layout_dot(L, c, coef32, p32, pc);
+        __builtin_nontemporal_store(qc, &q32[c]);
+        acc[0] += static_cast<double>(qc) * static_cast<double>(pc);
+    }
+    const int slots[1] = {kPartPq};
+    write_partials_at<1>(part, sp.grid, blk, slots, acc);
+}
+
+template <class Lay>
+__global__ void __launch_bounds__(kCellBlock)
+k_mx_amul_dot(SolverParams sp, Lay L, const float *__restrict__ coef32, const float *__restrict__ p32,
+              float *__restrict__ q32, double *__restrict__ part, const PcgState *__restrict__ st) {
+    mx_amul_dot(walk_share((st->inner_iter & 1) == 0), sp, L, coef32, p32, q32, part, st);
+}
+
+// the same product by the row walk (band layouts with two or more bands):
 // sp.grid_mx_amul workgroups, whose partials fill the start of the p.q slot
 // (slots sp.grid apart)
 template <int K>
@@ -569,8 +597,8 @@ __global__ void __launch_bounds__(kFinBlock) k_mx_finalize(SolverParams sp, cons
 }
 
 // ---------------------------------------------------------------------------
-// Meshes without a walk: two launches per inner iteration (the launches bound
-// it there: five of 4 to 6 us each before).  As in the FP64 solve's two-launch
+// Small and middling meshes without a walk: two launches per inner iteration
+// (the launches bound it there: five of 4 to 6 us each before).  As in the FP64 solve's two-launch
 // form the product forms the new direction where it reads it, and the sums'
 // second stage and the decisions are taken by every workgroup of the next
 // kernel.  Inner iteration i of the step (counted over its passes) keeps its
@@ -842,6 +870,32 @@ k_grp_direction_amul(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
     });
 }
 
+// members with five launches per inner iteration
+__global__ void __launch_bounds__(kCellBlock)
+k_grp_direction(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    for (int32_t b = s.share; b < min(s.end, m.sp.grid_mx); ++b) mx_direction(b, m.sp, m.r32, m.p32, m.d32, m.st);
+}
+
+__global__ void __launch_bounds__(kCellBlock)
+k_grp_amul_dot(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    with_member_layout(m, [&](auto L) {
+        for (int32_t b = s.share; b < min(s.end, m.sp.grid_mx); ++b)
+            mx_amul_dot(b, m.sp, L, m.coef32, m.p32, m.q32, m.part, m.st);
+    });
+}
+
+__global__ void __launch_bounds__(kCellBlock)
+k_grp_update_only(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
+    const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
+    const MemberDesc m = global_member(tab[gl.slot[s.member]]);
+    for (int32_t b = s.share; b < min(s.end, m.sp.grid_mx); ++b)
+        mx_update(b, m.sp, m.q32, m.sig32, m.r32, m.part, m.st);
+}
+
 __global__ void __launch_bounds__(kCellBlock)
 k_grp_update(const MemberDesc *__restrict__ tab, GroupLaunch gl) {
     const GroupShare s = group_share(gl, static_cast<int32_t>(blockIdx.x));
@@ -898,16 +952,17 @@ void launch_group_scale(const MemberDesc *tab, const GroupLaunch &cells, hipStre
                        cells);
 }
 
-// the first direction and product of the members' solves (big: those whose
-// decisions the one-workgroup kernels take)
+// the first direction and product of the solves of the members with two launches
+// per inner iteration (big: those whose decisions the one-workgroup kernels take)
 void launch_group_solve_start(const MemberDesc *tab, const GroupLaunch &gl, const GroupLaunch &big, hipStream_t s) {
     if (big.n) {
         launch_group_fin_start(tab, big, s);
         hipLaunchKernelGGL(k_grp_finalize<kMxInnerStart>, dim3(static_cast<unsigned>(big.n)), dim3(kFinBlock), 0, s,
                            tab, big);
     }
-    hipLaunchKernelGGL(k_grp_direction_amul<kMxSolve>, dim3(static_cast<unsigned>(gl.begin[gl.n])), dim3(kCellBlock),
-                       0, s, tab, gl);
+    if (gl.n)
+        hipLaunchKernelGGL(k_grp_direction_amul<kMxSolve>, dim3(static_cast<unsigned>(gl.begin[gl.n])),
+                           dim3(kCellBlock), 0, s, tab, gl);
 }
 
 // the end of a refinement pass: correction, FP64 residual; then the outer check
@@ -922,16 +977,27 @@ void launch_group_turn(const MemberDesc *tab, const GroupLaunch &cells, const Gr
         hipLaunchKernelGGL(k_grp_finalize<kMxOuter>, each, dim3(kFinBlock), 0, s, tab, big);
         hipLaunchKernelGGL(k_grp_finalize<kMxInnerStart>, each, dim3(kFinBlock), 0, s, tab, big);
     }
-    hipLaunchKernelGGL(k_grp_direction_amul<kMxPass>, dim3(static_cast<unsigned>(inner.begin[inner.n])),
-                       dim3(kCellBlock), 0, s, tab, inner);
+    if (inner.n)
+        hipLaunchKernelGGL(k_grp_direction_amul<kMxPass>, dim3(static_cast<unsigned>(inner.begin[inner.n])),
+                           dim3(kCellBlock), 0, s, tab, inner);
 }
 
-// one inner iteration of the launch's members (grid sizes from gl): the update,
-// the next direction and its product
-void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &gl, hipStream_t s) {
-    const dim3 cells(static_cast<unsigned>(gl.begin[gl.n]));
-    hipLaunchKernelGGL(k_grp_update, cells, dim3(kCellBlock), 0, s, tab, gl);
-    hipLaunchKernelGGL(k_grp_direction_amul<kMxNext>, cells, dim3(kCellBlock), 0, s, tab, gl);
+// one inner iteration of the launch's members: two launches for those of `gl`
+// (the update, the next direction and its product), five for those of `five`
+void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &gl, const GroupLaunch &five, hipStream_t s) {
+    if (gl.n) {
+        const dim3 cells(static_cast<unsigned>(gl.begin[gl.n]));
+        hipLaunchKernelGGL(k_grp_update, cells, dim3(kCellBlock), 0, s, tab, gl);
+        hipLaunchKernelGGL(k_grp_direction_amul<kMxNext>, cells, dim3(kCellBlock), 0, s, tab, gl);
+    }
+    if (five.n) {
+        const dim3 cells(static_cast<unsigned>(five.begin[five.n])), each(static_cast<unsigned>(five.n));
+        hipLaunchKernelGGL(k_grp_direction, cells, dim3(kCellBlock), 0, s, tab, five);
+        hipLaunchKernelGGL(k_grp_amul_dot, cells, dim3(kCellBlock), 0, s, tab, five);
+        hipLaunchKernelGGL(k_grp_finalize<kMxAlpha>, each, dim3(kFinBlock), 0, s, tab, five);
+        hipLaunchKernelGGL(k_grp_update_only, cells, dim3(kCellBlock), 0, s, tab, five);
+        hipLaunchKernelGGL(k_grp_finalize<kMxBeta>, each, dim3(kFinBlock), 0, s, tab, five);
+    }
 }
 
 void launch_group_gather(const MemberDesc *tab, const GroupLaunch &gl, PcgState *out, hipStream_t s) {
@@ -1029,10 +1095,16 @@ static void launch_inner_iteration(lf_problem *P, hipStream_t s) {
             }
         }
         constexpr int K = WalkBands<decltype(lay)>::value;
-        if constexpr (K > 0)
-            LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot_walk<K>,
-                      dim3(static_cast<unsigned>(P->sp.grid_mx_amul)), dim3(kCellBlock), 0, s, P->sp, lay,
-                      P->coef32, P->p32, P->q32, P->part, P->state);
+        if constexpr (K > 0) {
+            if (P->walk) {
+                LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot_walk<K>,
+                          dim3(static_cast<unsigned>(P->sp.grid_mx_amul)), dim3(kCellBlock), 0, s, P->sp, lay,
+                          P->coef32, P->p32, P->q32, P->part, P->state);
+                return;
+            }
+        }
+        LF_LAUNCH(P, LF_K_INNER_AMUL_DOT, s, k_mx_amul_dot<decltype(lay)>, mx_grid(P), dim3(kCellBlock), 0, s, P->sp,
+                  lay, P->coef32, P->p32, P->q32, P->part, P->state);
     });
     launch_mx_fin<kMxAlpha>(P, s);
     if (P->box32)
@@ -1277,7 +1349,7 @@ lf_status mixed_advance(lf_problem *P, SolveCtx &c, bool *finished, lf_solve_sta
         P->last_outer = h.n_outer;
         // the last residual left the sums of T (or, with no pass, the step's own are
         // still there); the row walk's does not
-        P->sumx_valid = P->sp.mx_rows > 0 || P->box;
+        P->sumx_valid = !P->walk || P->box;
         *finished = true;
         return LF_OK;
     }

@@ -107,13 +107,34 @@ constexpr int kFoldRows = 2;
 // up to this many rows its workgroups take contiguous shares per die: 100^3
 // 22.6 -> 20.2 us per product, 128^3 38.2 -> 38.5
 constexpr int32_t kFoldDieRows = 3 << 19;
-// The precision form's inner iteration without a walk: rows per thread such that
-// the partials per slot stay at most 2048 to 8 M rows (one row per thread, for
-// more workgroups, on small meshes); the start of a pass sums one partial per
-// 512 rows and four slots in every workgroup, which is too many above
-// kMxFoldStartRows, and the mean of x0 one slot above kMxFoldMeanRows.
+// The precision form's inner iteration without a walk: two launches, with so many
+// rows per thread that every workgroup sums at most 2048 partials per slot (one
+// row per thread, for more workgroups, on small meshes), up to kMxTwoBands rows in
+// the band layout and kMxTwoRows in the row layout; five launches with separate
+// reductions above.  The product that forms the direction where it reads it
+// reads two vectors at every neighbour: in the row layout that costs more
+// than the launches from 1.6 M rows on (random numbering, five steps, two / five
+// launches: 121^3 4.40 / 4.28 ms, 127^3 4.88 / 4.62, 160^3 9.12 / 8.87, 203^3
+// 19.5 / 18.8; three steps at 256^3 28.1 / 25.0), in the band layout it stays in
+// the caches (LF_WALK_OFF: 160^3 5.91 / 6.30 ms, 183^3 7.97 / 9.19) until the
+// vectors and the partials outgrow them (203^3 13.0 / 12.0, three steps at 256^3
+// 17.3 / 15.8).
+// The start of a pass sums one partial per 512 rows and four slots in every
+// workgroup, which is too many above kMxFoldStartRows, and the mean of x0 one
+// slot above kMxFoldMeanRows.
+constexpr int32_t kMxTwoBands = 15 << 19, kMxTwoRows = 3 << 19;
 constexpr int32_t kMxOneRow = 1 << 18, kMxFoldStartRows = 2 << 20, kMxFoldMeanRows = 1 << 20;
 constexpr int kMxManyRows = 8;
+// rows per thread of the two launches, 0: five launches
+constexpr int32_t mx_two_rows(int32_t n, bool bands) {
+    return n > (bands ? kMxTwoBands : kMxTwoRows) ? 0
+           : n <= kMxOneRow                       ? 1
+           : n <= kMxFoldStartRows                ? kMxRows
+                                                  : kMxManyRows;
+}
+static_assert(kMxOneRow <= 2048 * kCellBlock && kMxFoldStartRows <= 2048 * kCellBlock * kMxRows &&
+                  kMxTwoBands <= 2048 * kCellBlock * kMxManyRows && kMxTwoRows <= kMxFoldStartRows,
+              "at most 2048 partials per slot, which every workgroup sums");
 // the block walk's solves above this many partials per slot run on the
 // Jacobi-scaled matrix
 constexpr int32_t kScaledPartials = 512;
@@ -124,8 +145,8 @@ struct SolverParams {
     int32_t n;            // cells
     int32_t grid;         // workgroups of a cell-parallel launch (= partials per slot)
     int32_t grid_mx;      // workgroups of an FP32 inner-solve launch (mx_rows or kMxRows rows per thread)
-    int32_t mx_rows;      // precision form without a walk: two launches per inner iteration, this many
-                          // rows per thread; else 0
+    int32_t mx_rows;      // precision form: rows per thread of the two launches per inner iteration; 0: five
+                          // launches (a walk, or too many rows)
     int32_t mx_fold_start;// and the decisions at the start of a pass taken in the first of them
     int32_t n_red;        // DIC: first black cell
     int32_t max_outer;    // mixed: refinement passes cap

@@ -107,7 +107,7 @@ void launch_group_fin_start(const MemberDesc *tab, const GroupLaunch &gl, hipStr
 void launch_group_solve_start(const MemberDesc *tab, const GroupLaunch &inner, const GroupLaunch &big, hipStream_t s);
 void launch_group_turn(const MemberDesc *tab, const GroupLaunch &cells, const GroupLaunch &inner,
                        const GroupLaunch &big, hipStream_t s);
-void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &inner, hipStream_t s);
+void launch_group_iteration(const MemberDesc *tab, const GroupLaunch &inner, const GroupLaunch &five, hipStream_t s);
 void launch_group_gather(const MemberDesc *tab, const GroupLaunch &gl, PcgState *out, hipStream_t s);
 // non-orthogonal meshes: boundary values and gradient of T, then (correction:
 // on band meshes the assembly can form it instead) P->lap_src (lf_grad.hip);
