@@ -88,7 +88,8 @@ typedef int32_t lf_status;
                               box then take the block walk
                               (lf_problem_amul_walk), and so they do on any
                               box that gives the block walk enough workgroups
-                              of 256 threads: 1200 (2.5 M cells and up) in
+                              of 256 threads: 1200 (2.5 M cells and up; 2048,
+                              4.2 M, on x-lines of less than 32 cells) in
                               LF_PREC_FP64, 3600 (7.4 M) in LF_PREC_MIXED */
 #define LF_WALK_ON 1       /* the row walk whenever the layout allows it (tests) */
 #define LF_WALK_OFF 2      /* always one row per thread */

@@ -180,7 +180,9 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
         BoxWalk bw, bw32;
         const bool box_plan = box_walk_plan(m->N, m->n_bands, m->band_d, 2, &bw);
         P->too_large = wb >= kWalkMinBlocks || (box_plan && bw.blocks >= kGroupBoxBlocks);
-        const int32_t min_blocks = opts.precision == LF_PREC_MIXED ? kBoxMinBlocksMixed : kBoxMinBlocks;
+        const int32_t min_blocks = opts.precision == LF_PREC_MIXED ? kBoxMinBlocksMixed
+                                   : m->band_d[1] < kBoxMinLine    ? kBoxShortLineBlocks
+                                                                   : kBoxMinBlocks;
         if ((opts.amul_walk == LF_WALK_ON || wb >= kWalkMinBlocks || (box_plan && bw.blocks >= min_blocks)) &&
             wb <= P->sp.grid_mx) {
             P->walk = true;

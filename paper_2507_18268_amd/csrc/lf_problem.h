@@ -71,7 +71,13 @@ constexpr int kBwBlock = 256;       // threads of a block-walk workgroup
 // solve: 130^3 3.53 / 3.60 ms, 136^3 4.14 / 4.00, 150^3 5.77 / 5.42, 160^3
 // 7.08 / 6.51).  Precision form: from 7.4 M rows (168^3 6.70 / 7.10 ms, 184^3
 // 8.13 / 8.74, 200^3 11.95 both, 220^3 17.3 / 15.0).
+// On x-lines of less than 32 cells a wavefront of the walk holds parts of many
+// lines and the halo is most of its tiles: FP64 boxes with such lines take it from
+// 2048 workgroups (3.2 M rows, one row per thread / the walk's scaled solve: nx = 4
+// 29.1 / 36.4 ms, 8 16.2 / 19.6, 12 12.0 / 14.7, 24 8.92 / 9.05, 32 8.51 / 7.76, 34
+// 8.45 / 8.45, 42 8.29 / 7.96).
 constexpr int kBoxMinBlocks = 1200, kBoxMinBlocksMixed = 3600;
+constexpr int kBoxMinLine = 32, kBoxShortLineBlocks = 2048;
 // boxes from this many block-walk workgroups are too large for a group's member
 constexpr int kGroupBoxBlocks = 2048;
 // host-side plan of a block walk with W x-adjacent rows per lane
