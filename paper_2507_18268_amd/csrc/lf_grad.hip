@@ -307,10 +307,20 @@ __device__ __forceinline__ int64_t grad_share(int32_t n) {
 // are 1536 contiguous bytes, but one store per component writes every third
 // double of them: three partial writes of each line (192^3 213 us).  Where the
 // wavefront holds 64 consecutive cells it passes them through the LDS and
-// writes 512 bytes per store (205 us).  kLines false (up to kGradLineCells cells):
+// writes 512 bytes per store (205 us).  kLines false (grad_lines):
 // on small meshes, whose result stays in the caches, the detour only costs (its
 // registers a wave of occupancy): 80^3 16.0 us without, 16.4 with it, 90^3 21.7 / 21.6.
+// So it does where a wavefront seldom holds 64 consecutive cells, since the
+// runs along the widest band's offset D are short (whole calls, without / with it:
+// a line of 1 M cells 199 / 207 us, 48 x 20833 85 / 88, 160 x 6250 79 / 81, 200 x 5000
+// 75 / 76); above kGradDieCells the plain order that goes with it makes up
+// for that but for the shortest runs (1-D, 4 M cells 737 / 749 us, D = 3 660 / 677, D = 4
+// 539 / 516, D = 16 260 / 254).
 constexpr int32_t kGradLineCells = 5 << 17;
+constexpr int64_t kGradLineRun = 512, kGradPlainRun = 4;
+constexpr bool grad_lines(int32_t n, int64_t D) {
+    return n > kGradLineCells && D >= (n <= kGradDieCells ? kGradLineRun : kGradPlainRun);
+}
 static_assert(kGradLineCells <= kGradDieCells, "the form without lines takes runs per die");
 template <bool kLines>
 __device__ __forceinline__ void store_rows(double *__restrict__ grad, int64_t c, double gx, double gy, double gz) {
@@ -479,7 +489,7 @@ static void launch_grad_band(const lf_mesh *m, const double *T, const double *Tb
     const int64_t D = bo.d[K - 1];
     const int R = grad_walk_rows(m->N, D);
     const dim3 grid(static_cast<unsigned>(grad_walk_groups(m->N, D, R))), block(kGradBlock);
-    const bool lines = !step && m->N > kGradLineCells;
+    const bool lines = !step && grad_lines(m->N, D);
 #define LF_GRAD_BAND_NT(KK, RR, NT, LN)                                                                      \
     if (K == KK && R == RR && step == NT && lines == LN)                                                     \
         hipLaunchKernelGGL((k_grad_band<KK, RR, NT, LN>), grid, block, 0, s, m->N, bo, T, Tb, snb, m->gband,  \
