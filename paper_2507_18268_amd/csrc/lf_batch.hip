@@ -49,33 +49,44 @@ constexpr double kBatchTighten = 0.1;
 template <int BS>
 __device__ __forceinline__ double bsum1(double v) {
     double a[1] = {v};
-    block_sum<BS, 1>(a);
+    block_sum<BS, 1, BS == 1024>(a);
     return a[0];
 }
 
 template <int BS>
 __device__ __forceinline__ void bsum2(double &a0, double &a1) {
     double a[2] = {a0, a1};
-    block_sum<BS, 2>(a);
+    block_sum<BS, 2, BS == 1024>(a);
     a0 = a[0];
     a1 = a[1];
 }
 
-// Up to this many rows (kNear) a row's byte offset in any array fits the 32 bits
-// of an access's offset register, the rows that a last group reaches past the
-// end (at most 2^14) among them.  Addresses good for any row would cost 1-2%
-// with 512 threads and 9-18% with 1024, so larger problems have a form of their
-// own, one row after the other.
-constexpr int32_t kNearRows = (1 << 28) - (1 << 14);
+// Forms of the kernel, chosen for a launch by its largest problem (the results are
+// bitwise the same in each).
+//  kSmall: few rows per thread, one row per group (two with 256 threads) and fewer
+//    registers, so that more workgroups share a CU.  The large form's groups of
+//    up to 16 rows reach past the end of a small problem, and the rows there cost
+//    as much as real ones: 1024 requests of 8^3 to 12^3 with 256, 512, 1024 threads
+//    1.09, 1.22, 1.50 ms in this form, 1.64, 2.02, 1.94 in the large one; at 4096 rows
+//    both take the same (16^3, 512 threads 3.25 ms).
+//  kLarge: the others of up to kNearRows rows.
+//  kFar: beyond.  Up to kNearRows rows a row's byte offset in any array fits the 32
+//    bits of an access's offset register, the rows that a last group reaches past
+//    the end (at most 2^14) among them.  Addresses good for any row would cost
+//    1-2% with 512 threads and 9-18% with 1024, so larger problems go one row after
+//    the other.
+// Kernels of their own, since beside the far form in one kernel the large ran 2% slower.
+enum BatchForm : int { kLarge, kSmall, kFar };
+constexpr int32_t kSmallRows = 4096, kNearRows = (1 << 28) - (1 << 14);
 
 // fn(rows) for the thread's groups in order.  A group is an inner one if all its
 // rows are at least `halo` rows from both ends.
-template <int BS, int G, bool kNear, class Fn>
+template <int BS, int G, BatchForm kForm, class Fn>
 __device__ __forceinline__ void each_group(int32_t n, int32_t halo, Fn &&fn) {
     static_assert(G * BS <= 1 << 14, "kNearRows leaves room for one group");
     for (int32_t i = 0; i < n; i += G * BS) {
         const uint32_t c0 = static_cast<uint32_t>(i) + threadIdx.x;
-        if (kNear) __builtin_assume(c0 < (1u << 28));
+        if (kForm != kFar) __builtin_assume(c0 < (1u << 28));
         if (i >= halo && i + G * BS <= n - halo)
             fn(RowGroup<BS, G, true>{c0, n - 1});
         else
@@ -203,7 +214,7 @@ __device__ __forceinline__ void group_scale(const SellLayout &L, const RowGroup<
 //
 // The task's arrays are distinct allocations: taking them into __restrict__
 // locals lets the compiler overlap the loads of several rows of a loop.
-template <int BS, int kLds, bool kNear, class Lay>
+template <int BS, int kLds, BatchForm kForm, class Lay>
 __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, int32_t n_steps,
                                            lf_solve_stats *__restrict__ stats, float *lds) {
     const int32_t n = tk.n;
@@ -235,15 +246,16 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
     // about a microsecond and the next group's loads are not issued before: as
     // many rows as the registers (131072 / BS per thread) hold loads for, in
     // the FP32 vector updates (kG), the FP32 product (kGP), the FP64 product
-    // (kG64) and the assembly (kGA).
-    constexpr int kG = !kNear ? 1 : BS == 1024 ? 8 : 16, kGP = !kNear ? 1 : BS == 1024 ? 4 : 8;
-    constexpr int kG64 = !kNear ? 1 : BS == 1024 ? 2 : 4, kGA = !kNear || BS == 1024 ? 1 : 4;
+    // (kG64) and the assembly (kGA).  The other forms: see BatchForm.
+    constexpr int kFew = kForm == kSmall && BS == 256 ? 2 : 1;
+    constexpr int kG = kForm != kLarge ? kFew : BS == 1024 ? 8 : 16, kGP = kForm != kLarge ? kFew : BS == 1024 ? 4 : 8;
+    constexpr int kG64 = kForm != kLarge ? 1 : BS == 1024 ? 2 : 4, kGA = kForm != kLarge || BS == 1024 ? 1 : 4;
     constexpr bool kBand = !std::is_same_v<Lay, SellLayout>;
     int32_t halo = n;                 // rows between a row and its farthest neighbour (rows: unknown)
     if constexpr (kBand) halo = L.d[2];
     // sum of x0 = T; the later steps' is taken with the last residual
     double sx = 0.0;
-    each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
+    each_group<BS, kG, kForm>(n, 0, [&](const auto &g) {
         double x[kG];
 #pragma unroll
         for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
@@ -294,7 +306,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             a_nf += fabs(ax - pa) + fabs(sb - pa);
         };
         if constexpr (kBand) {
-            each_group<BS, kGA, kNear>(n, halo, [&](const auto &g) {
+            each_group<BS, kGA, kForm>(n, halo, [&](const auto &g) {
                 double a[kGA][6], xv[kGA][6], lap[kGA], v[kGA], xc[kGA], bd[kGA], bs[kGA];
                 int32_t b0[kGA], b1[kGA];
 #pragma unroll
@@ -351,13 +363,13 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
         }
         {
             double a[4] = {a_r, a_nf, s_r, s_wr};
-            block_sum<BS, 4>(a);
+            block_sum<BS, 4, BS == 1024>(a);
             a_r = a[0];
             a_nf = a[1];
             s_r = a[2];
             s_wr = a[3];
         }
-        each_group<BS, kG64, kNear>(n, halo, [&](const auto &g) { group_scale(L, g, t32, coef, coef32); });
+        each_group<BS, kG64, kForm>(n, halo, [&](const auto &g) { group_scale(L, g, t32, coef, coef32); });
         const double nf = a_nf + 1e-20;
         const double res0 = a_r / nf;
         double res = res0;
@@ -376,7 +388,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             while (!inner_done) {
                 if (inner_iter > 0) {          // p = rs in the first iteration
                     const float fb = static_cast<float>(beta);
-                    each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
+                    each_group<BS, kG, kForm>(n, 0, [&](const auto &g) {
                         float rs[kG], pc[kG];
 #pragma unroll
                         for (int u = 0; u < kG; ++u) {
@@ -389,7 +401,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
                     __syncthreads();
                 }
                 double s_pq = 0.0;
-                each_group<BS, kGP, kNear>(n, halo, [&](const auto &g) {
+                each_group<BS, kGP, kForm>(n, halo, [&](const auto &g) {
                     float pc[kGP], qc[kGP];
 #pragma unroll
                     for (int u = 0; u < kGP; ++u) pc[u] = g.at(p, u);
@@ -407,7 +419,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
                 const double alpha = wArA / pq;
                 const float fa = static_cast<float>(alpha);
                 double u_r = 0.0, u_wr = 0.0;
-                each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
+                each_group<BS, kG, kForm>(n, 0, [&](const auto &g) {
                     float sc[kG], pc[kG], rs[kG], q[kG], y[kG];
 #pragma unroll
                     for (int u = 0; u < kG; ++u) {
@@ -443,7 +455,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             }
             if (nonfinite) break;
             // T += d, then the FP64 true residual (and the sum of T)
-            each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
+            each_group<BS, kG, kForm>(n, 0, [&](const auto &g) {
                 double x[kG];
                 float tc[kG], y[kG];
 #pragma unroll
@@ -459,7 +471,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             __syncthreads();
             double o_r = 0.0, o_x = 0.0;
             s_r = s_wr = 0.0;
-            each_group<BS, kG64, kNear>(n, halo, [&](const auto &g) {
+            each_group<BS, kG64, kForm>(n, halo, [&](const auto &g) {
                 double xc[kG64], ax[kG64], b[kG64], y[kG64];
                 float sc[kG64], tc[kG64];
 #pragma unroll
@@ -484,7 +496,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
             });
             {
                 double a[4] = {o_r, o_x, s_r, s_wr};
-                block_sum<BS, 4>(a);
+                block_sum<BS, 4, BS == 1024>(a);
                 o_r = a[0];
                 o_x = a[1];
                 s_r = a[2];
@@ -500,7 +512,7 @@ __device__ __forceinline__ void solve_task(const BatchTask &tk, const Lay &L, in
         if (tk.snap) {
             double *__restrict__ out = as_global(tk.snap) + static_cast<int64_t>(step) * n;
             const int32_t *__restrict__ ip = as_global(tk.iperm);
-            each_group<BS, kG, kNear>(n, 0, [&](const auto &g) {
+            each_group<BS, kG, kForm>(n, 0, [&](const auto &g) {
                 double x[kG];
 #pragma unroll
                 for (int u = 0; u < kG; ++u) x[u] = g.at(T, u);
@@ -542,10 +554,7 @@ __host__ __device__ inline int lds_vectors(int32_t n) {
     return n > kRows ? 0 : kRows / n < 4 ? kRows / n : 4;
 }
 
-// kNear: no task has more than kNearRows rows; else all run in the other form
-// (bitwise the same results; a kernel of its own, since beside it in one kernel
-// the near forms ran 2% slower)
-template <int BS, bool kNear>
+template <int BS, BatchForm kForm>
 __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ tasks, int32_t n_tasks,
                                              int32_t *__restrict__ counter, int32_t n_steps,
                                              lf_solve_stats *__restrict__ stats) {
@@ -566,15 +575,17 @@ __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ task
             for (int k = 0; k < 3; ++k) L.d[k] = tk.band_d[k];
             L.mag_sf = as_global(tk.band_mag_sf);
             L.delta = as_global(tk.band_delta);
-            if constexpr (!kNear) {
-                solve_task<BS, 0, false>(tk, L, n_steps, st, nullptr);
+            if constexpr (kForm == kFar) {
+                solve_task<BS, 0, kForm>(tk, L, n_steps, st, nullptr);
+            } else if constexpr (kForm == kSmall) {
+                solve_task<BS, 4, kForm>(tk, L, n_steps, st, lds);
             } else {
                 switch (lds_vectors(tk.n)) {
-                    case 0: solve_task<BS, 0, true>(tk, L, n_steps, st, nullptr); break;
-                    case 1: solve_task<BS, 1, true>(tk, L, n_steps, st, lds); break;
-                    case 2: solve_task<BS, 2, true>(tk, L, n_steps, st, lds); break;
-                    case 3: solve_task<BS, 3, true>(tk, L, n_steps, st, lds); break;
-                    default: solve_task<BS, 4, true>(tk, L, n_steps, st, lds); break;
+                    case 0: solve_task<BS, 0, kForm>(tk, L, n_steps, st, nullptr); break;
+                    case 1: solve_task<BS, 1, kForm>(tk, L, n_steps, st, lds); break;
+                    case 2: solve_task<BS, 2, kForm>(tk, L, n_steps, st, lds); break;
+                    case 3: solve_task<BS, 3, kForm>(tk, L, n_steps, st, lds); break;
+                    default: solve_task<BS, 4, kForm>(tk, L, n_steps, st, lds); break;
                 }
             }
         } else {
@@ -582,7 +593,7 @@ __global__ void __launch_bounds__(BS) k_batch(const BatchTask *__restrict__ task
                                         as_global(tk.rlen)},
                                as_global(tk.mag_sf), as_global(tk.delta), as_global(tk.emag_sf),
                                as_global(tk.edelta)};
-            solve_task<BS, 0, kNear>(tk, L, n_steps, st, nullptr);
+            solve_task<BS, 0, kForm>(tk, L, n_steps, st, nullptr);
         }
     }
 }
@@ -610,10 +621,10 @@ struct lf_batch {
 // the kernel with the LDS of the launch's largest need (above 64 KiB it has to
 // be allowed first)
 template <int BS>
-static lf_status launch_batch(bool near, int32_t lds_rows, int32_t grid, int32_t n, int32_t n_steps, lf_batch *b,
+static lf_status launch_batch(BatchForm form, int32_t lds_rows, int32_t grid, int32_t n, int32_t n_steps, lf_batch *b,
                               hipStream_t s) {
-    const int lds = near ? static_cast<int>(sizeof(float)) * lds_rows : 0;
-    auto kern = near ? k_batch<BS, true> : k_batch<BS, false>;
+    const int lds = form != kFar ? static_cast<int>(sizeof(float)) * lds_rows : 0;
+    auto kern = form == kFar ? k_batch<BS, kFar> : form == kSmall ? k_batch<BS, kSmall> : k_batch<BS, kLarge>;
     if (lds > (48 << 10))
         LF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    156 << 10));
@@ -709,7 +720,7 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         }
     }
     int32_t lds_rows = 0;     // the launch's LDS, in floats
-    bool near = true;
+    int32_t most = 0;         // rows of its largest problem
     for (int32_t i = 0; i < n; ++i) {
         const lf_problem *P = problems[i];
         if (!P) { set_error("problem %d is NULL", i); return LF_EINVAL; }
@@ -750,18 +761,19 @@ lf_status lf_batch_launch(lf_batch *b, int32_t n, lf_problem *const *problems, d
         t.n = m->N; t.max_iter = P->sp.max_iter; t.max_outer = P->sp.max_outer;
         t.n_bfaces = m->B;
         if (t.nb == 3) lds_rows = std::max(lds_rows, lds_vectors(t.n) * t.n);
-        near = near && t.n <= kNearRows;
+        most = std::max(most, t.n);
     }
     for (int32_t i = 0; i < n; ++i) problems[i]->sumx_valid = false;     // the launch rewrites T
+    const BatchForm form = most > kNearRows ? kFar : most <= kSmallRows ? kSmall : kLarge;
     hipStream_t s = b->stream;
     int32_t g = n_workgroups > 0 ? std::min(n_workgroups, n) : n;
     LF_HIP(hipMemcpyAsync(b->d_tasks, b->h_tasks, sizeof(BatchTask) * n, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, s, b->d_counter);
     LF_HIP(hipEventRecord(b->start, s));
     switch (block_threads) {
-        case 256: LF_TRY(launch_batch<256>(near, lds_rows, g, n, n_steps, b, s)); break;
-        case 512: LF_TRY(launch_batch<512>(near, lds_rows, g, n, n_steps, b, s)); break;
-        default: LF_TRY(launch_batch<1024>(near, lds_rows, g, n, n_steps, b, s)); break;
+        case 256: LF_TRY(launch_batch<256>(form, lds_rows, g, n, n_steps, b, s)); break;
+        case 512: LF_TRY(launch_batch<512>(form, lds_rows, g, n, n_steps, b, s)); break;
+        default: LF_TRY(launch_batch<1024>(form, lds_rows, g, n, n_steps, b, s)); break;
     }
     LF_HIP(hipGetLastError());
     LF_HIP(hipMemcpyAsync(b->h_stats, b->d_stats, sizeof(lf_solve_stats) * static_cast<size_t>(n) * n_steps,

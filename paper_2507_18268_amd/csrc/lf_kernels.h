@@ -62,7 +62,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Sum of NQ values over a workgroup of BS threads, result in every thread;
 // fixed order (wave butterflies, then the wave sums in wave order).
-template <int BS, int NQ>
+// kLean: the wave sums are read four at a time.  At once (the loads are otherwise
+// all moved ahead of the sums) four sums of 16 waves take 128 registers, all that a
+// thread of 1024 has.
+template <int BS, int NQ, bool kLean = false>
 __device__ __forceinline__ void block_sum(double (&v)[NQ]) {
     constexpr int kWaves = BS / 64;
     __shared__ double red[NQ][kWaves];
@@ -78,7 +81,11 @@ __device__ __forceinline__ void block_sum(double (&v)[NQ]) {
     for (int q = 0; q < NQ; ++q) {
         double s = red[q][0];
 #pragma unroll
-        for (int j = 1; j < kWaves; ++j) s += red[q][j];
+        for (int j = 1; j < kWaves; ++j) {
+            if (kLean && j % 4 == 0) asm volatile("" : "+v"(s) : : "memory");
+            s += red[q][j];
+        }
+        if (kLean) asm volatile("" : "+v"(s) : : "memory");
         v[q] = s;
     }
     __syncthreads();
