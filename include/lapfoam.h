@@ -536,7 +536,7 @@ lf_status lf_group_poll(lf_group *group, lf_problem **finished, int32_t max_fini
 #define LF_K_COMMIT 2        /* last pending x += alpha p of a solve */
 #define LF_K_DIRECTION 3     /* p = w + beta p, deferred x += alpha p */
 #define LF_K_AMUL_DOT 4      /* q = A p, p.q partials; FP64 diagonal solves of up to
-                                2 M rows: the direction update is part of it, and
+                                2.6 M rows: the direction update is part of it, and
                                 the reductions of it and of the update */
 #define LF_K_UPDATE 5        /* r -= alpha q, |r| and w.r partials */
 #define LF_K_DIC_RD 6        /* DIC diagonal */
@@ -544,7 +544,8 @@ lf_status lf_group_poll(lf_group *group, lf_problem **finished, int32_t max_fini
 #define LF_K_DIC_BACKWARD 8  /* DIC backward sweep (red rows) + w.r partials */
 #define LF_K_MIXED_RESIDUAL 9   /* mixed: FP64 residual r = b - A T, |r| partials */
 #define LF_K_MIXED_CORRECT 10   /* mixed: T += d, FP32 copies */
-#define LF_K_INNER_DIRECTION 11 /* mixed: FP32 direction update */
+#define LF_K_INNER_DIRECTION 11 /* mixed: FP32 direction update (part of the product
+                                   where an inner iteration is two launches) */
 #define LF_K_INNER_AMUL_DOT 12  /* mixed: FP32 q = A p, FP64 p.q partials */
 #define LF_K_INNER_UPDATE 13    /* mixed: FP32 update, FP64 partials */
 #define LF_K_MIXED_PREP 14      /* mixed: FP32 coefficients of the scaled matrix

@@ -224,9 +224,9 @@ lf_status lf_problem_create(const lf_mesh *m, const lf_patch_bc *bcs, double DT,
         }
     }
     // FP64 diagonal solves without a walk, up to kFoldMaxRows rows: two launches
-    // per iteration.  Their partials per slot stay at most 2048, which every
-    // workgroup sums (4 per thread): one row per thread while that holds
-    // (more workgroups), then kFoldRows in the product and kUpdRows in the update.
+    // per iteration, whose workgroups each sum all partials (at most 2560 per slot, 5
+    // per thread): one row per thread up to kFoldOneRow (more workgroups), then
+    // kFoldRows in the product and kUpdRows in the update.
     const bool fp64_diag = opts.precision == LF_PREC_FP64 && opts.precond == LF_PC_DIAGONAL && !P->rb;
     P->fold = fp64_diag && !P->walk && m->N <= kFoldMaxRows;
     if (P->fold) {

@@ -9,7 +9,8 @@
 // initial decision, start of the first refinement pass), the turn from one
 // refinement pass to the next (correction, FP64 residual, outer check, start
 // of the next pass: no-ops once the solve is done), then a block of inner FP32
-// iterations of every iterating member (two launches each), and the gather of
+// iterations of every iterating member (two launches each, five for members of
+// more rows than the two pay for), and the gather of
 // the members' solver states into one array in the host's memory.  From those states the host
 // decides each member's next move: keep iterating, turn to the next pass, or
 // finish the step (statistics, snapshot of T, next step or end of the run).

@@ -1297,7 +1297,7 @@ static lf_status launch_inner(lf_problem *P, int32_t k) {
     return LF_OK;
 }
 
-// block of k inner iterations (k may be 0), then the state copy and ev[2]
+// block of k inner iterations (k may be 0), the state for the host, then ev[2]
 static lf_status mixed_block(lf_problem *P, SolveCtx &c) {
     hipStream_t s = P->stream;
     prof_lead(P, s);

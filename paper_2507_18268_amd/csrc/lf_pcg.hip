@@ -3,9 +3,11 @@
 // Cell-parallel kernels run one row per thread over the whole mesh (the
 // hardware dispatcher balances workgroups over the CUs), gather through the
 // sliced row layout (no atomics, so results are deterministic) and leave one
-// partial sum per workgroup; one-workgroup kernels then sum the partials in a
-// fixed order and take every scalar decision of the solver (step lengths,
-// convergence, singularity), so the cell-parallel kernels only read the state.
+// partial sum per workgroup.  On large meshes one-workgroup kernels then sum the
+// partials in a fixed order and take every scalar decision of the solver (step
+// lengths, convergence, singularity), and the cell-parallel kernels only read the
+// state; on the others every workgroup of the next cell-parallel kernel does, and
+// its workgroup 0 writes the state while they read it (the rule: PcgState).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -2490,7 +2492,6 @@ static lf_status launch_iterations(lf_problem *P, int32_t k) {
     return LF_OK;
 }
 
-// block of k iterations, then the state copy and ev[2]
 // end of a solve (does nothing while the solve is not done); hst: where the
 // state goes for the host, or null
 static void launch_commit(lf_problem *P, hipStream_t s, PcgState *hst) {
@@ -2509,6 +2510,7 @@ void launch_publish(lf_problem *P, hipStream_t s) {
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, P->state, P->d_hstate);
 }
 
+// block of k iterations, the commit and the state for the host, then ev[2]
 static lf_status fp64_block(lf_problem *P, SolveCtx &c) {
     hipStream_t s = P->stream;
     c.k = std::min<int32_t>(c.k, std::max<int32_t>(1, P->sp.max_iter + 1 - c.launched));

@@ -20,8 +20,12 @@ enum PartialSlot : int {
     kNumPart = 8
 };
 
-// Solver state on the device.  Written only by the one-workgroup reduction
-// kernels; the cell-parallel kernels only read it.
+// Solver state on the device.  Written by the one-workgroup reduction kernels and,
+// where an iteration is two launches, by workgroup 0 of the cell-parallel ones
+// while the other workgroups read it.  There a value that a launch overwrites is
+// read by the others only from a copy which the launch before made (the _prev
+// members); done and inner_done are read once per workgroup, and a workgroup that
+// already sees workgroup 0's new value takes the decision that value records.
 struct PcgState {
     double nf;            // normalisation factor
     double res0;          // initial normalised residual
@@ -110,6 +114,8 @@ constexpr int kMaxGraphLog = 6;   // largest captured block: 64 iterations
 // kFoldRows in the product
 constexpr int32_t kFoldMaxRows = 5 << 19, kFoldOneRow = 1 << 19;
 constexpr int kFoldRows = 2;
+static_assert(kFoldOneRow <= 1024 * kCellBlock && kFoldMaxRows <= 2560 * kCellBlock * kFoldRows,
+              "at most 1024 and 2560 partials per slot, which every workgroup sums");
 // up to this many rows its workgroups take contiguous shares per die: 100^3
 // 22.6 -> 20.2 us per product, 128^3 38.2 -> 38.5
 constexpr int32_t kFoldDieRows = 3 << 19;
@@ -207,7 +213,8 @@ struct lf_problem {
     lf::BoxWalk bw32{};
     bool rb2 = false;                          // DIC's kernels on the two-colour layout: two pairs per lane
     bool sumx_valid = false;                   // the part array holds the partial sums of the current T
-                                               // (written by the FP64 commit; any other write of T clears it)
+                                               // (the FP64 commit's or the precision form's last residual's,
+                                               // alone or in a group; any other write of T clears it)
     bool fold = false;                         // diagonal FP64 solves of up to kFoldMaxRows rows: two launches
                                                // per iteration (directions alternate between p and p2)
     bool scaled = false;                       // diagonal FP64 solves on the block walk: CG on

@@ -116,10 +116,10 @@ void launch_nonorth_source(lf_problem *P, hipStream_t s, bool correction = true)
 lf_status launch_problem_grad(lf_problem *P, double *grad, double *bgrad);
 // A solve is driven in two halves so that one host loop can drive several
 // problems on their own streams: *_start enqueues the set-up and the first
-// block of iterations, followed by an async copy of the solver state and
-// P->ev[2]; once that event has completed, *_advance reads the state and
-// either enqueues the next block (again ending with the copy and ev[2]) or
-// reports the solve finished, its stats in *out.
+// block of iterations, whose last kernel writes the solver state to the host's
+// copy, and P->ev[2]; once that event has completed, *_advance reads the state
+// and either enqueues the next block (ending in the same way) or reports the
+// solve finished, its stats in *out.
 struct SolveCtx {
     int32_t fixed_k = 0;   // iterations per block when fixed (>0), else adaptive
     int32_t k = 0;         // iterations of the next block
