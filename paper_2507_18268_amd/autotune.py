@@ -14,7 +14,8 @@ with the most solves per second is kept.
 Results are cached in a JSON file keyed by the GPU architecture and the form,
 so the choice is stable from run to run (a problem's result depends on the
 workgroup size and on its lane, so a fixed table also keeps results
-reproducible).
+reproducible).  A stored table stands until the tuner is run again: run it after
+a change of the kernels it chooses between.
 """
 import json
 import os
