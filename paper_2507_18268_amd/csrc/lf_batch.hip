@@ -50,14 +50,14 @@ constexpr double kBatchTighten = 0.1;
 template <int BS>
 __device__ __forceinline__ double bsum1(double v) {
     double a[1] = {v};
-    block_sum<BS, 1, BS == 1024>(a);
+    block_sum<BS, 1>(a);
     return a[0];
 }
 
 template <int BS>
 __device__ __forceinline__ void bsum2(double &a0, double &a1) {
     double a[2] = {a0, a1};
-    block_sum<BS, 2, BS == 1024>(a);
+    block_sum<BS, 2>(a);
     a0 = a[0];
     a1 = a[1];
 }
@@ -68,8 +68,8 @@ __device__ __forceinline__ void bsum2(double &a0, double &a1) {
 //    registers, so that more workgroups share a CU.  The large form's groups of
 //    up to 16 rows reach past the end of a small problem, and the rows there cost
 //    as much as real ones: 1024 requests of 8^3 to 12^3 with 256, 512, 1024 threads
-//    1.09, 1.22, 1.50 ms in this form, 1.64, 2.02, 1.94 in the large one; at 4096 rows
-//    both take the same (16^3, 512 threads 3.25 ms).
+//    1.08, 1.25, 1.47 ms in this form, 1.64, 2.02, 1.94 in the large one; at 4096 rows
+//    both take the same (16^3, 512 threads 3.3 ms).
 //  kLarge: the others of up to kNearRows rows.
 //  kFar: beyond.  Up to kNearRows rows a row's byte offset in any array fits the 32
 //    bits of an access's offset register, the rows that a last group reaches past
