@@ -243,7 +243,7 @@ k_assemble(SolverParams sp, double rdt, double DT, Lay L, const int32_t *__restr
 // kernel's expressions in its order (the matrix is bitwise the same); the
 // partials are per workgroup, with zeros in the rest of each slot, which the
 // reduction reads.  At 256^3, against one row per thread: precision form 532 ->
-// 414 us (2.0 GB, 4.9 TB/s), scaled solve 502 -> 470 us (2.2 GB, 4.7 TB/s).
+// 417 us (2.0 GB, 4.8 TB/s), scaled solve 502 -> 470 us (2.2 GB, 4.7 TB/s).
 template <bool kMixed>
 __global__ void __launch_bounds__(kCellBlock)
 k_assemble_pair(SolverParams sp, double rdt, double DT, BandLayout<3> L, const int32_t *__restrict__ bface_start,
