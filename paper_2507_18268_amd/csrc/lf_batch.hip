@@ -204,7 +204,7 @@ __device__ __forceinline__ void group_scale(const SellLayout &L, const RowGroup<
 // preconditioned CG of A d = r; it stops on the L1 norm of A's residual,
 // sum s|rs| with s = sqrt(diagB).  r and y are scaled with t in FP64: rounded, it
 // left T up to 13% further from the exact step at the same residual (16^3 to 24^3,
-// against 3 to 7% nearer than CG on the unscaled matrix now) for 2 to 4% of the time.
+// against 6% nearer than CG on the unscaled matrix now) for 2 to 4% of the time.
 //
 // What bounds it is what one workgroup's CU can fetch past its L1: 32 bytes per
 // clock, 75 GB/s, whatever level answers (the 68 bytes per row of an inner
